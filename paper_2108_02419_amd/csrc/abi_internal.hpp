@@ -116,6 +116,28 @@ inline int setup_competitor(const bbe_competitor& c, float L, int idx, bbe::Race
     return BBE_OK;
 }
 
+// Fills the race's step bounds (see RaceConst) from its competitors and time
+// terms: R = alpha + beta*d (+ gamma*min(t, tau)) is at most 1 + |rho| (+
+// gamma*tau) for d in [0, L], a free step at most R*(elo + espan), and a
+// blocked one at most R times a step of the tick before.  Rounded up by
+// 2^-10, which covers the roundings of eight ticks.
+inline void set_step_bounds(bbe_race& r) {
+    double cap = 0.0, rm = 1.0;
+    for (int c = 0; c < r.n; ++c) {
+        cap = std::fmax(cap, (double)r.rc.elo[c] + 0x1p16 * (double)r.rc.espan16[c]);
+        const double drift = (double)r.pace.gamma[c] * (double)r.pace.tau[c];
+        rm = std::fmax(rm, 1.0 + std::fabs((double)r.comp[c].rho) + (drift > 0.0 ? drift : 0.0));
+    }
+    double sum = 0.0, pw = 1.0;
+    for (int i = 1; i <= 8; ++i) {
+        pw *= rm;
+        sum += pw;
+        if (i == 2) r.rc.reach2 = (float)(sum * (1.0 + 0x1p-10));
+    }
+    r.rc.reach8 = (float)(sum * (1.0 + 0x1p-10));
+    r.rc.step_cap = (float)(cap * (1.0 + 0x1p-10));
+}
+
 // Puts a state (competitor order) into slot order: positions ascending,
 // equal positions by competitor index (a stable insertion sort).
 inline void to_slot_order(int n, const float* d, const float* s, float* d_out, float* s_out,

@@ -50,13 +50,13 @@ constexpr uint32_t kPfxWaveU = kMaxN * 256;
 constexpr uint32_t kPfxLanePar = kMaxN * 32;
 
 template <int N>
-__device__ void run_prefix_lane(const ReqDesc& rq, char* smem, uint32_t ucol, uint32_t pbase,
+__device__ void run_prefix_lane(const ReqDesc& rq, uint32_t ucol, uint32_t pbase,
                                 int lane, uint32_t k0, uint32_t k1, uint32_t* tick_out,
                                 float* pos_out, float* prev_out) {
     for (int c = 0; c < N; ++c) {
-        float4* rec = reinterpret_cast<float4*>(smem + pbase + c * 32);
-        rec[0] = make_float4(rq.rc.elo[c], rq.rc.espan16[c], rq.rc.alpha[c], rq.rc.beta[c]);
-        rec[1] = make_float4(rq.rc.theta[c], rq.pace.gamma[c], rq.pace.tau[c], 0.0f);
+        const uint32_t rec = pbase + kRecSize * c;
+        lds_st(rec, f32x4{rq.rc.elo[c], rq.rc.espan16[c], rq.rc.alpha[c], rq.rc.beta[c]});
+        lds_st(rec + kRecHalf<N>, f32x4{rq.rc.theta[c], rq.pace.gamma[c], rq.pace.tau[c], 0.0f});
     }
     Slots<N> sl;
     slots_reset<N>(sl, rq.d0, rq.s0, rq.id0, pbase);
@@ -69,7 +69,7 @@ __device__ void run_prefix_lane(const ReqDesc& rq, char* smem, uint32_t ucol, ui
             break;
         }
         uint32_t cross =
-            slots_tick<N, kPaceInline>(sl, smem, ucol, pbase, rq.rc.L, t, rq.prefix_sim, rq.request, k0,
+            slots_tick<N, kPaceInline>(sl, ucol, pbase, rq.rc.L, t, rq.prefix_sim, rq.request, k0,
                                 k1);
         t += 1;
         if (cross) {
@@ -95,14 +95,14 @@ __global__ void __launch_bounds__(64) prefix_batch_kernel(const ReqDesc* __restr
     const int i = blockIdx.x * 64 + lane;
     if (i >= n_reqs) return;
     const ReqDesc& rq = reqs[i];
-    const uint32_t ucol = lane * 4;
-    const uint32_t pbase = kPfxWaveU + lane * kPfxLanePar;
+    const uint32_t ucol = lds_addr(smem) + lane * 4;
+    const uint32_t pbase = lds_addr(smem) + kPfxWaveU + lane * kPfxLanePar;
     float* po = pos_out + (size_t)i * kMaxN;
     float* pv = prev_out + (size_t)i * kMaxN;
     switch (rq.rc.n) {
 #define BBE_CASE(n) \
     case n:         \
-        run_prefix_lane<n>(rq, smem, ucol, pbase, lane, k0, k1, tick_out + i, po, pv); \
+        run_prefix_lane<n>(rq, ucol, pbase, lane, k0, k1, tick_out + i, po, pv); \
         break;
         BBE_CASE(1) BBE_CASE(2) BBE_CASE(3) BBE_CASE(4) BBE_CASE(5)
         BBE_CASE(6) BBE_CASE(7) BBE_CASE(8) BBE_CASE(9) BBE_CASE(10)

@@ -30,19 +30,10 @@ __device__ __forceinline__ unsigned long long wave_sum_u64b(unsigned long long v
 }
 
 // Parked slots stop being stepped 2 at a time once every lane has parked
-// them, from N = 6 on.  From N = 18 on, the copies of the tick fit in the
-// registers only with ranking and parking in one pass (slots_rank_park).
-// The paced variant skips 4 at a time for N = 12 .. 17 only: it spills
-// from N = 18 on either way.
-template <int N, bool kPaced>
+// them, from N = 6 on.
+template <int N>
 constexpr int batch_skip_step() {
-    if constexpr (kPaced) return (N >= 12 && N <= 17) ? 4 : 0;
     return N >= 6 ? 2 : 0;
-}
-
-template <int N, bool kPaced>
-constexpr bool batch_rank_park() {
-    return !kPaced && N >= 18;
 }
 
 template <int N, bool kPaced>
@@ -50,31 +41,31 @@ __device__ __forceinline__ void run_chunk(const ReqDesc& rq, const Chunk& ch, ch
                                           uint32_t wbase, int lane, uint32_t k0, uint32_t k1,
                                           unsigned long long* wins_row,
                                           unsigned long long& steps) {
-    const uint32_t ucol = wbase + lane * 4;
-    const uint32_t icol = wbase + kWaveU + kWavePar + kWaveHist + kWaveInit + lane;
-    const uint32_t pbase = wbase + kWaveU;
+    const uint32_t ubase = lds_addr(smem) + wbase;
+    const uint32_t ibase = ubase + kWaveU + kWavePar + kWaveHist + kWaveInit;
+    const uint32_t pbase = ubase + kWaveU;
     uint32_t* hist = reinterpret_cast<uint32_t*>(smem + wbase + kWaveU + kWavePar);
     float* d0 = reinterpret_cast<float*>(smem + wbase + kWaveU + kWavePar + kWaveHist);
     float* s0 = d0 + kMaxN;
     uint8_t* id0 = reinterpret_cast<uint8_t*>(s0 + kMaxN);
-    write_params<N>(smem, pbase, rq.rc, lane);
-    if constexpr (kPaced) write_pace<N>(smem, pbase, rq.pace, lane);
+    write_params<N>(pbase, rq.rc, lane);
+    if constexpr (kPaced) write_pace<N>(pbase, rq.pace, lane);
     if (lane < N) {
         hist[lane] = 0u;
         d0[lane] = rq.d0[lane];
         s0[lane] = rq.s0[lane];
         id0[lane] = rq.id0[lane];
     }
+    const StepBounds sb{rq.rc.step_cap, rq.rc.reach2, rq.rc.reach8};
     for (uint32_t g = 0; g < ch.count; g += 64) {
         const bool live = g + lane < ch.count;
-        const uint32_t sim = rq.sim_begin + ch.first + g + lane;
+        const uint32_t sim0 = rq.sim_begin + ch.first + g;
         // re-read the start state from LDS each generation rather than
         // keeping 3N registers live across the loop
         __asm__ volatile("" ::: "memory");
-        run_generation<N, kPaced ? kPaceTable : kPaceOff, batch_rank_park<N, kPaced>(),
-                       batch_skip_step<N, kPaced>()>(
-            smem, ucol, icol, pbase, rq.rc.L, d0, s0, id0, rq.t0, live, sim, rq.request, k0, k1,
-            rq.stop_after, nullptr, hist, steps);
+        run_generation<N, kPaced ? kPaceTable : kPaceOff, batch_skip_step<N>()>(
+            ubase, ibase, pbase, rq.rc.L, sb, d0, s0, id0, rq.t0, live, sim0, rq.request, k0,
+            k1, rq.stop_after, kNoRow, hist, steps);
     }
     if (lane < N) {
         uint32_t w = hist[lane];
@@ -107,7 +98,8 @@ template <bool kPaced>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
     batch_mc_kernel(const BatchArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];  // waves * kWaveBytes
-    const int wave = threadIdx.x >> 6;
+    // the same in every lane of a wave, which the compiler cannot tell
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const uint32_t wbase = wave * kWaveBytes;
     unsigned long long steps = 0ull;

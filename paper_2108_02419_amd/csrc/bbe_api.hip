@@ -93,6 +93,7 @@ BBE_API int bbe_race_init(const bbe_competitor* comp, int n, float track_len, bb
             return rc;
         }
     }
+    set_step_bounds(*r);
     *out = r;
     return ok();
 }
@@ -122,6 +123,7 @@ BBE_API int bbe_race_set_pace(bbe_race* race, const float* gamma, const float* t
         if (gamma[c] != 0.0f) paced = 1;
     }
     race->pace.paced = paced;
+    set_step_bounds(*race);
     return ok();
 }
 

@@ -36,7 +36,7 @@ template <int N>
 __device__ __forceinline__ void slots_store_pos(const Slots<N>& sl, uint32_t pbase,
                                                 float* __restrict__ row) {
 #pragma unroll
-    for (int k = 0; k < N; ++k) row[(sl.rec[k] - pbase) >> 5] = sl.d[k];
+    for (int k = 0; k < N; ++k) row[(sl.rec[k] - pbase) >> 4] = sl.d[k];
 }
 
 template <int N>
@@ -44,24 +44,25 @@ __global__ void __launch_bounds__(64) race_trace_kernel(const TraceArgs a) {
     constexpr uint32_t kPar = ((N * 256 + 1023) / 1024) * 1024;
     __shared__ __attribute__((aligned(1024))) char smem[kPar + 1024];
     const int lane = threadIdx.x;
-    const uint32_t ucol = lane * 4;
-    write_params<N>(smem, kPar, a.rc, lane);
-    write_pace<N>(smem, kPar, a.pace, lane);
+    const uint32_t ucol = lds_addr(smem) + lane * 4;
+    const uint32_t pbase = lds_addr(smem) + kPar;
+    write_params<N>(pbase, a.rc, lane);
+    write_pace<N>(pbase, a.pace, lane);
     __syncthreads();
     if (lane != 0) return;
     Slots<N> sl;
-    slots_reset<N>(sl, a.d0, a.s0, a.id0, kPar);
-    slots_store_pos<N>(sl, kPar, a.trace);
+    slots_reset<N>(sl, a.d0, a.s0, a.id0, pbase);
+    slots_store_pos<N>(sl, pbase, a.trace);
     uint32_t rows = 1;
     uint32_t t = a.t0;
     // at most max_rows - 1 <= 2^20 ticks
     while (rows < a.max_rows) {
         const uint32_t cross =
-            slots_tick<N, kPaceInline>(sl, smem, ucol, kPar, a.rc.L, t, a.sim, a.request, a.k0, a.k1);
+            slots_tick<N, kPaceInline>(sl, ucol, pbase, a.rc.L, t, a.sim, a.request, a.k0, a.k1);
         if (cross) break;
         t += 1;
         slots_restore<N>(sl);
-        slots_store_pos<N>(sl, kPar, a.trace + (size_t)rows * N);
+        slots_store_pos<N>(sl, pbase, a.trace + (size_t)rows * N);
         ++rows;
     }
     *a.rows_out = rows;

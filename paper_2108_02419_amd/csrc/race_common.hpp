@@ -31,6 +31,11 @@ struct RaceConst {
     float alpha[kMaxN];
     float beta[kMaxN];
     float theta[kMaxN];
+    // bounds of a step, rounded up: a free step is at most step_cap * R, R at
+    // most some r >= 1; reach2 and reach8 are r + r^2 and r + ... + r^8
+    float step_cap;
+    float reach2;
+    float reach8;
 };
 
 // Time term of R (R += fl(gamma * min(t, tau)) on the absolute tick t);

@@ -24,13 +24,14 @@ __global__ void __launch_bounds__(64) race_prefix_kernel(const PrefixArgs a) {
     constexpr uint32_t kPar = ((N * 256 + 1023) / 1024) * 1024;
     __shared__ __attribute__((aligned(1024))) char smem[kPar + 1024];
     const int lane = threadIdx.x;
-    const uint32_t ucol = lane * 4;
-    write_params<N>(smem, kPar, a.rc, lane);
-    write_pace<N>(smem, kPar, a.pace, lane);
+    const uint32_t ucol = lds_addr(smem) + lane * 4;
+    const uint32_t pbase = lds_addr(smem) + kPar;
+    write_params<N>(pbase, a.rc, lane);
+    write_pace<N>(pbase, a.pace, lane);
     __syncthreads();
     if (lane != 0) return;
     Slots<N> sl;
-    slots_reset<N>(sl, a.d0, a.s0, a.id0, kPar);
+    slots_reset<N>(sl, a.d0, a.s0, a.id0, pbase);
     uint32_t t = a.t0;
     bool ok = true;
     for (;;) {
@@ -41,7 +42,7 @@ __global__ void __launch_bounds__(64) race_prefix_kernel(const PrefixArgs a) {
             break;
         }
         uint32_t cross =
-            slots_tick<N, kPaceInline>(sl, smem, ucol, kPar, a.rc.L, t, a.sim, a.request, a.k0, a.k1);
+            slots_tick<N, kPaceInline>(sl, ucol, pbase, a.rc.L, t, a.sim, a.request, a.k0, a.k1);
         t += 1;
         if (cross) {
             ok = false;
@@ -50,7 +51,7 @@ __global__ void __launch_bounds__(64) race_prefix_kernel(const PrefixArgs a) {
         slots_restore<N>(sl);
     }
     *a.tick_out = ok ? t : 0xFFFFFFFFu;
-    slots_store<N>(sl, kPar, a.pos_out, a.prev_out);
+    slots_store<N>(sl, pbase, a.pos_out, a.prev_out);
 }
 
 __global__ void zero_u64_kernel(unsigned long long* __restrict__ p, int n) {

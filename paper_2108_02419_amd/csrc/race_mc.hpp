@@ -69,15 +69,16 @@ __global__ void __launch_bounds__(kBlock)
     __attribute__((amdgpu_waves_per_eu(mc_waves_per_eu<N, kPaced>()))) race_mc_kernel(const SimArgs a) {
     using Lay = BlockLds<N, kPaced>;
     __shared__ __attribute__((aligned(1024))) char smem[Lay::kBytes];
-    const int wave = threadIdx.x >> 6;
+    // the same in every lane of a wave, which the compiler cannot tell
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    const uint32_t ucol = Lay::kU + wave * (N * 256) + lane * 4;
-    const uint32_t icol = Lay::kIds + wave * (N * 64) + lane;
+    const uint32_t base = lds_addr(smem);
+    const uint32_t ubase = base + Lay::kU + wave * (N * 256);
+    const uint32_t ibase = base + Lay::kIds + wave * (N * 64);
     // plain: one record table for the workgroup (every wave simulates the
     // same race), at a compile-time offset; paced: one table per wave
     const uint32_t pbase =
-        kPaced ? Lay::kPar + (uint32_t)__builtin_amdgcn_readfirstlane(wave) * (N * 32u)
-               : Lay::kPar;
+        base + (kPaced ? Lay::kPar + (uint32_t)wave * (N * 32u) : Lay::kPar);
     uint32_t* s_wins = reinterpret_cast<uint32_t*>(smem + Lay::kWins);
     unsigned long long* s_steps = reinterpret_cast<unsigned long long*>(smem + Lay::kSteps);
 
@@ -85,10 +86,10 @@ __global__ void __launch_bounds__(kBlock)
     float* s_s0 = s_d0 + kMaxN;
     uint8_t* s_id0 = reinterpret_cast<uint8_t*>(s_s0 + kMaxN);
     if constexpr (kPaced) {
-        write_params<N>(smem, pbase, a.rc, lane);
-        write_pace<N>(smem, pbase, a.pace, lane);
+        write_params<N>(pbase, a.rc, lane);
+        write_pace<N>(pbase, a.pace, lane);
     } else {
-        write_params<N>(smem, pbase, a.rc, (int)threadIdx.x);
+        write_params<N>(pbase, a.rc, (int)threadIdx.x);
     }
     if (threadIdx.x < N) {
         s_wins[threadIdx.x] = 0u;
@@ -100,23 +101,23 @@ __global__ void __launch_bounds__(kBlock)
     __syncthreads();
 
     const float L = a.rc.L;
+    const StepBounds sb{a.rc.step_cap, a.rc.reach2, a.rc.reach8};
     const uint64_t wave_stride = (uint64_t)gridDim.x * kWaves * 64;
     unsigned long long steps = 0ull;
 
     // finish orders go to the wave's LDS table during a generation and to
     // HBM in one coalesced flush at its end
     char* otab = smem + Lay::kOrd + wave * (64 * N);
-    for (uint64_t base = ((uint64_t)blockIdx.x * kWaves + wave) * 64; base < a.n_sims;
-         base += wave_stride) {
-        const uint64_t j = base + lane;
-        const bool live = j < a.n_sims;
-        uint8_t* row = (a.orders && live) ? reinterpret_cast<uint8_t*>(otab + lane * N) : nullptr;
+    for (uint64_t first = ((uint64_t)blockIdx.x * kWaves + wave) * 64; first < a.n_sims;
+         first += wave_stride) {
+        const bool live = first + lane < a.n_sims;
         // re-read the start state from LDS each generation rather than
         // keeping it live (in registers) across the loop
         __asm__ volatile("" ::: "memory");
-        run_generation<N, kPaced ? kPaceTable : kPaceOff, true, mc_skip_step<N>()>(
-            smem, ucol, icol, pbase, L, s_d0, s_s0, s_id0, a.t0, live, a.sim_begin + (uint32_t)j,
-            a.request, a.k0, a.k1, a.stop_after, row, s_wins, steps);
+        run_generation<N, kPaced ? kPaceTable : kPaceOff, mc_skip_step<N>()>(
+            ubase, ibase, pbase, L, sb, s_d0, s_s0, s_id0, a.t0, live,
+            a.sim_begin + (uint32_t)first, a.request, a.k0, a.k1, a.stop_after,
+            a.orders ? lds_addr(otab) : kNoRow, s_wins, steps);
         if (a.orders) {
             // the wave's LDS operations complete in order; keep the compiler
             // from moving the table's reads above the lanes' writes (and the
@@ -124,8 +125,8 @@ __global__ void __launch_bounds__(kBlock)
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const uint64_t rows = a.n_sims - base < 64 ? a.n_sims - base : 64;
-            flush_orders(otab, a.orders + base * N, (uint32_t)(rows * N), lane);
+            const uint64_t rows = a.n_sims - first < 64 ? a.n_sims - first : 64;
+            flush_orders(otab, a.orders + first * N, (uint32_t)(rows * N), lane);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
