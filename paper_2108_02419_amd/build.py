@@ -19,8 +19,8 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libbbe.so")
 SOURCES = ["race_kernels.hip", "race_kernels_paced.hip", "batch_kernels.hip",
            "batch_kernels_paced.hip", "mlp_kernels.hip", "order_kernels.hip",
-           "bettor_kernels.hip", "bbe_api.hip", "bbe_batch.hip", "bbe_mlp.hip",
-           "bbe_bettors.hip"]
+           "bettor_kernels.hip", "team_kernels.hip", "bbe_api.hip", "bbe_batch.hip",
+           "bbe_mlp.hip", "bbe_bettors.hip"]
 ARCH = os.environ.get("BBE_OFFLOAD_ARCH", "gfx950")
 
 

@@ -43,78 +43,6 @@ __global__ void batch_probs_kernel(const unsigned long long* __restrict__ wins,
     probs[r * kMaxN + c] = p;
 }
 
-// In-play states for a batch: lane i advances simulation prefix_sim of
-// request i until its leader reaches the target.  Each lane has its own
-// race, so each lane has its own parameter records.
-constexpr uint32_t kPfxWaveU = kMaxN * 256;
-constexpr uint32_t kPfxLanePar = kMaxN * 32;
-
-template <int N>
-__device__ void run_prefix_lane(const ReqDesc& rq, uint32_t ucol, uint32_t pbase,
-                                int lane, uint32_t k0, uint32_t k1, uint32_t* tick_out,
-                                float* pos_out, float* prev_out) {
-    for (int c = 0; c < N; ++c) {
-        const uint32_t rec = pbase + kRecSize * c;
-        lds_st(rec, f32x4{rq.rc.elo[c], rq.rc.espan16[c], rq.rc.alpha[c], rq.rc.beta[c]});
-        lds_st(rec + kRecHalf<N>, f32x4{rq.rc.theta[c], rq.pace.gamma[c], rq.pace.tau[c], 0.0f});
-    }
-    Slots<N> sl;
-    slots_reset<N>(sl, rq.d0, rq.s0, rq.id0, pbase);
-    uint32_t t = rq.t0;
-    bool ok = true;
-    for (;;) {
-        if (sl.d[N - 1] >= rq.target) break;
-        if (t - rq.t0 >= kTickLimit) {
-            ok = false;
-            break;
-        }
-        uint32_t cross =
-            slots_tick<N, kPaceInline>(sl, ucol, pbase, rq.rc.L, t, rq.prefix_sim, rq.request, k0,
-                                k1);
-        t += 1;
-        if (cross) {
-            ok = false;
-            break;
-        }
-        slots_restore<N>(sl);
-    }
-    *tick_out = ok ? t : 0xFFFFFFFFu;
-    for (int c = 0; c < kMaxN; ++c) {
-        pos_out[c] = 0.0f;
-        prev_out[c] = 0.0f;
-    }
-    slots_store<N>(sl, pbase, pos_out, prev_out);
-}
-
-__global__ void __launch_bounds__(64) prefix_batch_kernel(const ReqDesc* __restrict__ reqs,
-                                                          int n_reqs, uint32_t k0, uint32_t k1,
-                                                          uint32_t* tick_out, float* pos_out,
-                                                          float* prev_out) {
-    __shared__ __attribute__((aligned(16))) char smem[kPfxWaveU + 64 * kPfxLanePar];
-    const int lane = threadIdx.x;
-    const int i = blockIdx.x * 64 + lane;
-    if (i >= n_reqs) return;
-    const ReqDesc& rq = reqs[i];
-    const uint32_t ucol = lds_addr(smem) + lane * 4;
-    const uint32_t pbase = lds_addr(smem) + kPfxWaveU + lane * kPfxLanePar;
-    float* po = pos_out + (size_t)i * kMaxN;
-    float* pv = prev_out + (size_t)i * kMaxN;
-    switch (rq.rc.n) {
-#define BBE_CASE(n) \
-    case n:         \
-        run_prefix_lane<n>(rq, ucol, pbase, lane, k0, k1, tick_out + i, po, pv); \
-        break;
-        BBE_CASE(1) BBE_CASE(2) BBE_CASE(3) BBE_CASE(4) BBE_CASE(5)
-        BBE_CASE(6) BBE_CASE(7) BBE_CASE(8) BBE_CASE(9) BBE_CASE(10)
-        BBE_CASE(11) BBE_CASE(12) BBE_CASE(13) BBE_CASE(14) BBE_CASE(15)
-        BBE_CASE(16) BBE_CASE(17) BBE_CASE(18) BBE_CASE(19) BBE_CASE(20)
-#undef BBE_CASE
-        default:
-            tick_out[i] = 0xFFFFFFFFu;
-            break;
-    }
-}
-
 // ---------------------------------------------------------------- launchers
 
 hipError_t launch_batch_mc(const BatchArgs& a, int waves_per_block, int grid, bool paced,
@@ -156,15 +84,6 @@ hipError_t launch_batch_probs(const unsigned long long* wins, const ReqDesc* req
     long total = (long)n_reqs * kMaxN;
     hipLaunchKernelGGL(batch_probs_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,
                        wins, reqs, n_reqs, probs);
-    return hipGetLastError();
-}
-
-hipError_t launch_prefix_batch(const ReqDesc* reqs, int n_reqs, uint32_t k0, uint32_t k1,
-                               uint32_t* tick_out, float* pos_out, float* prev_out,
-                               hipStream_t s) {
-    if (n_reqs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(prefix_batch_kernel, dim3((n_reqs + 63) / 64), dim3(64), 0, s, reqs, n_reqs,
-                       k0, k1, tick_out, pos_out, prev_out);
     return hipGetLastError();
 }
 

@@ -1,12 +1,6 @@
-// bettor_kernels.hip -- the in-play side of the model on gfx950: the trace
-// of the race that bettors watch (paper Section 3: the race state is the
-// vector of positions, advanced tick by tick by Eq. 1) and the views of the
-// cheap bettor rules of Section 5 (LinEx, LW, UD, ZI) over that trace.
-//
-// race_trace_kernel<N>: one lane advances one simulation with the same
-// slot code as the Monte-Carlo kernels and writes the positions after every
-// tick, stopping before the first tick in which a competitor reaches the
-// line (the winner market closes then).
+// bettor_kernels.hip -- the in-play side of the model on gfx950: the views of
+// the cheap bettor rules of paper Section 5 (LinEx, LW, UD, ZI) over the
+// trace of the race that bettors watch.
 //
 // bettor_views_kernel: one thread per bettor, a block of 256 bettors over
 // chunks of kViewRowsPerBlock trace rows.  The bettors are stored grouped by
@@ -31,42 +25,6 @@
 #include <utility>
 
 namespace bbe {
-
-template <int N>
-__device__ __forceinline__ void slots_store_pos(const Slots<N>& sl, uint32_t pbase,
-                                                float* __restrict__ row) {
-#pragma unroll
-    for (int k = 0; k < N; ++k) row[(sl.rec[k] - pbase) >> 4] = sl.d[k];
-}
-
-template <int N>
-__global__ void __launch_bounds__(64) race_trace_kernel(const TraceArgs a) {
-    constexpr uint32_t kPar = ((N * 256 + 1023) / 1024) * 1024;
-    __shared__ __attribute__((aligned(1024))) char smem[kPar + 1024];
-    const int lane = threadIdx.x;
-    const uint32_t ucol = lds_addr(smem) + lane * 4;
-    const uint32_t pbase = lds_addr(smem) + kPar;
-    write_params<N>(pbase, a.rc, lane);
-    write_pace<N>(pbase, a.pace, lane);
-    __syncthreads();
-    if (lane != 0) return;
-    Slots<N> sl;
-    slots_reset<N>(sl, a.d0, a.s0, a.id0, pbase);
-    slots_store_pos<N>(sl, pbase, a.trace);
-    uint32_t rows = 1;
-    uint32_t t = a.t0;
-    // at most max_rows - 1 <= 2^20 ticks
-    while (rows < a.max_rows) {
-        const uint32_t cross =
-            slots_tick<N, kPaceInline>(sl, ucol, pbase, a.rc.L, t, a.sim, a.request, a.k0, a.k1);
-        if (cross) break;
-        t += 1;
-        slots_restore<N>(sl);
-        slots_store_pos<N>(sl, pbase, a.trace + (size_t)rows * N);
-        ++rows;
-    }
-    *a.rows_out = rows;
-}
 
 // Leader and runner-up of one row (ties to the lowest index) and the
 // distance between them; p2 = p1 and gap = 0 when n = 1.
@@ -223,24 +181,6 @@ __global__ void zero_u32_kernel(uint32_t* __restrict__ p, size_t n) {
 }
 
 // ---------------------------------------------------------------- launchers
-
-template <int N>
-static hipError_t launch_trace_n(const TraceArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(race_trace_kernel<N>, dim3(1), dim3(64), 0, s, a);
-    return hipGetLastError();
-}
-
-template <int... I>
-static hipError_t dispatch_trace(int n, const TraceArgs& a, hipStream_t s,
-                                 std::integer_sequence<int, I...>) {
-    using Fn = hipError_t (*)(const TraceArgs&, hipStream_t);
-    static constexpr Fn table[] = {launch_trace_n<I + 1>...};
-    return table[n - 1](a, s);
-}
-
-hipError_t launch_race_trace(const TraceArgs& a, hipStream_t s) {
-    return dispatch_trace(a.rc.n, a, s, std::make_integer_sequence<int, kMaxN>{});
-}
 
 hipError_t launch_bettor_views(const ViewArgs& a, hipStream_t s) {
     if (a.n_eval == 0 || a.n_bettors == 0) return hipSuccess;

@@ -18,42 +18,6 @@
 
 namespace bbe {
 
-// One lane advances one simulation until the leader reaches the target.
-template <int N>
-__global__ void __launch_bounds__(64) race_prefix_kernel(const PrefixArgs a) {
-    constexpr uint32_t kPar = ((N * 256 + 1023) / 1024) * 1024;
-    __shared__ __attribute__((aligned(1024))) char smem[kPar + 1024];
-    const int lane = threadIdx.x;
-    const uint32_t ucol = lds_addr(smem) + lane * 4;
-    const uint32_t pbase = lds_addr(smem) + kPar;
-    write_params<N>(pbase, a.rc, lane);
-    write_pace<N>(pbase, a.pace, lane);
-    __syncthreads();
-    if (lane != 0) return;
-    Slots<N> sl;
-    slots_reset<N>(sl, a.d0, a.s0, a.id0, pbase);
-    uint32_t t = a.t0;
-    bool ok = true;
-    for (;;) {
-        if (sl.d[N - 1] >= a.target) break;  // slots ascending: the leader is last
-        if (t - a.t0 >= a.max_ticks) break;
-        if (t - a.t0 >= kTickLimit) {
-            ok = false;
-            break;
-        }
-        uint32_t cross =
-            slots_tick<N, kPaceInline>(sl, ucol, pbase, a.rc.L, t, a.sim, a.request, a.k0, a.k1);
-        t += 1;
-        if (cross) {
-            ok = false;
-            break;
-        }
-        slots_restore<N>(sl);
-    }
-    *a.tick_out = ok ? t : 0xFFFFFFFFu;
-    slots_store<N>(sl, pbase, a.pos_out, a.prev_out);
-}
-
 __global__ void zero_u64_kernel(unsigned long long* __restrict__ p, int n) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0ull;
@@ -89,12 +53,6 @@ static int occupancy_n() {
     return nb > 0 ? nb : 1;
 }
 
-template <int N>
-static hipError_t launch_prefix_n(const PrefixArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(race_prefix_kernel<N>, dim3(1), dim3(64), 0, s, a);
-    return hipGetLastError();
-}
-
 template <int... I>
 static hipError_t dispatch_mc(int n, const SimArgs& a, int grid, hipStream_t s,
                               std::integer_sequence<int, I...>) {
@@ -108,14 +66,6 @@ static int dispatch_occ(int n, std::integer_sequence<int, I...>) {
     using Fn = int (*)();
     static constexpr Fn table[] = {occupancy_n<I + 1>...};
     return table[n - 1]();
-}
-
-template <int... I>
-static hipError_t dispatch_prefix(int n, const PrefixArgs& a, hipStream_t s,
-                                  std::integer_sequence<int, I...>) {
-    using Fn = hipError_t (*)(const PrefixArgs&, hipStream_t);
-    static constexpr Fn table[] = {launch_prefix_n<I + 1>...};
-    return table[n - 1](a, s);
 }
 
 using Seq = std::make_integer_sequence<int, kMaxN>;
@@ -132,10 +82,6 @@ int mc_blocks_per_cu(int n, bool paced) {
 hipError_t launch_race_mc(const SimArgs& a, int grid, hipStream_t s) {
     if (a.pace.paced) return launch_race_mc_paced(a, grid, s);
     return dispatch_mc(a.rc.n, a, grid, s, Seq{});
-}
-
-hipError_t launch_race_prefix(const PrefixArgs& a, hipStream_t s) {
-    return dispatch_prefix(a.rc.n, a, s, Seq{});
 }
 
 hipError_t launch_zero_u64(unsigned long long* p, int n, hipStream_t s) {

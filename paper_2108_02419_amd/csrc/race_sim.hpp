@@ -36,8 +36,7 @@
 //      slot order.
 //
 // slots_tick does this in full.  The Monte-Carlo kernels use it only where two
-// positions are equal, and slots_tick_plain (below) everywhere else; the
-// kernels that run a single simulation always use it.
+// positions are equal, and slots_tick_plain (below) everywhere else.
 #pragma once
 
 #include "race_common.hpp"
@@ -95,21 +94,17 @@ __device__ __forceinline__ float parked() {
     return __uint_as_float(0x7FC00000u);
 }
 
-// How slots_tick adds the time term gamma*min(t, tau) of R:
-//   kPaceOff    no time term (gamma = 0 everywhere);
-//   kPaceInline every slot reads its competitor's gamma and tau and forms the
-//               term itself (lanes may be at different ticks);
-//   kPaceTable  all lanes of the wave are at the same tick: lane c forms
-//               competitor c's term once per tick into its record, and every
-//               slot adds it.  The term is the same rounded product either
-//               way, so the three modes agree bit for bit.
-enum Pace : int { kPaceOff = 0, kPaceInline = 1, kPaceTable = 2 };
+// How a tick adds the time term gamma*min(t, tau) of R: not at all (gamma = 0
+// everywhere), or from a table: all lanes of the wave are at the same tick, so
+// lane c forms competitor c's term once per tick into its record and every
+// slot adds it.
+enum Pace : int { kPaceOff = 0, kPaceTable = 1 };
 
 // Parameter records: competitor c's (elo, espan16, alpha, beta) at
-// pbase + 16*c and (theta, gamma | term, tau, gamma) at the same distance from
-// the second half of the table; the time-term fields are written (by the same
-// lane, afterwards) by write_pace, their second word holds gamma for
-// kPaceInline and the current tick's term for kPaceTable.  In two halves
+// pbase + 16*c and (theta, term, tau, gamma) at the same distance from the
+// second half of the table; tau and gamma are written (by the same lane,
+// afterwards) by write_pace, the current tick's term by write_pace_terms.
+// In two halves
 // because the slots of a wave read 64 records at once: at 16 bytes apart two
 // of up to 16 competitors never share a bank, at 32 bytes competitors eight
 // apart did (bank conflicts 28 -> 13% of the cycles at 20 competitors).
@@ -133,7 +128,6 @@ __device__ __forceinline__ void write_pace(uint32_t pbase, const RacePace& pc,
                                           int lane) {
     if (lane < N) {
         const uint32_t rec = pbase + kRecSize * lane + kRecHalf<N>;
-        lds_st(rec + 4u, pc.gamma[lane]);
         lds_st(rec + 8u, pc.tau[lane]);
         lds_st(rec + 12u, pc.gamma[lane]);
     }
@@ -200,7 +194,6 @@ __device__ __forceinline__ uint32_t slots_tick(Slots<N>& sl, uint32_t ucol,
                                                uint32_t pbase, float L, uint32_t t,
                                                uint32_t sim, uint32_t request, uint32_t k0,
                                                uint32_t k1) {
-    const float tf = (float)t;
     if constexpr (kPace == kPaceTable) {
         write_pace_terms<N>(pbase, t);
     }
@@ -217,19 +210,14 @@ __device__ __forceinline__ uint32_t slots_tick(Slots<N>& sl, uint32_t ucol,
     //    and parameter record are read from LDS kPf slots ahead of use.
     const uint32_t ubias = ucol - 16u * pbase;
     constexpr int kPf = 4;
-    float pu[N], pth[N], pga[N], pta[N];
+    float pu[N], pth[N], pga[N];
     f32x4 pp[N];
 #pragma unroll
     for (int k = N - 1; k >= 0 && k >= N - kPf; --k) {
         const uint32_t rec = sl.rec[k];
         pu[k] = lds_ld<float>(ubias + (rec << 4));
         pp[k] = lds_ld<f32x4>(rec);
-        if constexpr (kPace == kPaceInline) {
-            const f32x4 q = lds_ld<f32x4>(rec + kRecHalf<N>);
-            pth[k] = q.x;
-            pga[k] = q.y;
-            pta[k] = q.z;
-        } else if constexpr (kPace == kPaceTable) {
+        if constexpr (kPace == kPaceTable) {
             const f32x2 q = lds_ld<f32x2>(rec + kRecHalf<N>);
             pth[k] = q.x;
             pga[k] = q.y;  // the term itself
@@ -246,12 +234,7 @@ __device__ __forceinline__ uint32_t slots_tick(Slots<N>& sl, uint32_t ucol,
             const uint32_t rec = sl.rec[k - kPf];
             pu[k - kPf] = lds_ld<float>(ubias + (rec << 4));
             pp[k - kPf] = lds_ld<f32x4>(rec);
-            if constexpr (kPace == kPaceInline) {
-                const f32x4 q = lds_ld<f32x4>(rec + kRecHalf<N>);
-                pth[k - kPf] = q.x;
-                pga[k - kPf] = q.y;
-                pta[k - kPf] = q.z;
-            } else if constexpr (kPace == kPaceTable) {
+            if constexpr (kPace == kPaceTable) {
                 const f32x2 q = lds_ld<f32x2>(rec + kRecHalf<N>);
                 pth[k - kPf] = q.x;
                 pga[k - kPf] = q.y;
@@ -267,7 +250,6 @@ __device__ __forceinline__ uint32_t slots_tick(Slots<N>& sl, uint32_t ucol,
         // Eq. 1
         const f32x4 p = pp[k];
         float R = p.z + p.w * d;
-        if constexpr (kPace == kPaceInline) R = R + pga[k] * fminf(tf, pta[k]);
         if constexpr (kPace == kPaceTable) R = R + pga[k];
         float x = p.x + p.y * pu[k];
         // min of two positive steps (ns = 0 only when nobody is ahead)
@@ -600,7 +582,6 @@ __device__ __forceinline__ void slots_tick_plain(Slots<N>& sl, const float (&gap
                                                  uint32_t ucol, uint32_t pbase, uint32_t t,
                                                  uint32_t sim, uint32_t request, uint32_t k0,
                                                  uint32_t k1) {
-    static_assert(kPace != kPaceInline, "lanes of a wave share the tick");
     if constexpr (kPace == kPaceTable) write_pace_terms<N>(pbase, t);
     write_draws<N>(ucol, t, sim, request, k0, k1);
     const uint32_t ubias = ucol - 16u * pbase;
@@ -856,19 +837,6 @@ __device__ __forceinline__ void run_generation(uint32_t ubase, uint32_t ibase, u
         } while (__builtin_amdgcn_ballot_w64(live) && slots_tied<N>(sl));
     }
     steps += run;
-}
-
-// Writes a lane's state in competitor order (prefix runs).
-template <int N>
-__device__ __forceinline__ void slots_store(const Slots<N>& sl, uint32_t pbase,
-                                            float* __restrict__ pos_out,
-                                            float* __restrict__ prev_out) {
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        const uint32_t c = (sl.rec[k] - pbase) >> 4;
-        pos_out[c] = sl.d[k];
-        prev_out[c] = sl.s[k];
-    }
 }
 
 }  // namespace bbe
