@@ -18,8 +18,10 @@ struct bbe_mlp {
     float* grad = nullptr;
     uint16_t *w1 = nullptr, *w2 = nullptr, *w3 = nullptr, *w4 = nullptr;
     uint16_t *w2t = nullptr, *w3t = nullptr, *w4t = nullptr;
-    uint16_t *h1 = nullptr, *h2 = nullptr, *h3 = nullptr;
+    // activations and gradients of a training batch, fragment order
+    uint16_t *xf = nullptr, *h1 = nullptr, *h2 = nullptr, *h3 = nullptr;
     uint16_t *dz4 = nullptr, *dz3 = nullptr, *dz2 = nullptr, *dz1 = nullptr;
+    float* loss_part = nullptr;  // [workgroups of a training batch]
     bbe::WgradTile* tiles = nullptr;
     int n_tiles = 0;
     float* wpart = nullptr;  // [chunks of kWgRows rows][kNParams], when max_batch > kWgRows
@@ -33,8 +35,8 @@ void destroy(bbe_mlp* m) {
     if (!m) return;
     if (m->params) (void)hipDeviceSynchronize();
     void* ptrs[] = {m->params, m->m,   m->v,   m->grad, m->w1,  m->w2,  m->w3,  m->w4,
-                    m->w2t,    m->w3t, m->w4t, m->h1,   m->h2,  m->h3,  m->dz4, m->dz3,
-                    m->dz2,    m->dz1, m->tiles, m->wpart};
+                    m->w2t,    m->w3t, m->w4t, m->xf,   m->h1,  m->h2,  m->h3,  m->dz4,
+                    m->dz3,    m->dz2, m->dz1, m->loss_part, m->tiles, m->wpart};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     delete m;
@@ -51,6 +53,9 @@ bbe::MlpAdamArgs adam_args(bbe_mlp* m, const float* grad, float lr) {
     a.m = m->m;
     a.v = m->v;
     a.grad = grad;
+    a.part = nullptr;
+    a.n_parts = 0;
+    a.grad_out = nullptr;
     a.lr = lr;
     a.beta1 = kBeta1;
     a.beta2 = kBeta2;
@@ -68,8 +73,8 @@ bbe::MlpAdamArgs adam_args(bbe_mlp* m, const float* grad, float lr) {
     return a;
 }
 
-bbe::MlpFwdArgs fwd_args(const bbe_mlp* m, const uint16_t* x, const int32_t* nv, int B) {
-    bbe::MlpFwdArgs a;
+bbe::MlpArgs fwd_args(const bbe_mlp* m, const uint16_t* x, const int32_t* nv, int B) {
+    bbe::MlpArgs a;
     std::memset(&a, 0, sizeof a);
     a.x = x;
     a.n_valid = nv;
@@ -98,7 +103,8 @@ BBE_API int bbe_mlp_create(const float* params, int max_batch, bbe_mlp** out) {
     bbe_mlp* m = new (std::nothrow) bbe_mlp();
     if (!m) return fail(BBE_ENOMEM, "out of host memory");
     m->max_batch = max_batch;
-    const size_t B = (size_t)max_batch;
+    // whole blocks of 32 rows
+    const size_t B = ((size_t)max_batch + 31) / 32 * 32;
     bool okk = alloc(&m->params, bbe::kNParams) && alloc(&m->m, bbe::kNParams) &&
                alloc(&m->v, bbe::kNParams) && alloc(&m->grad, bbe::kNParams) &&
                alloc(&m->w1, (size_t)bbe::kHid * bbe::kIn) &&
@@ -111,7 +117,8 @@ BBE_API int bbe_mlp_create(const float* params, int max_batch, bbe_mlp** out) {
                alloc(&m->h1, B * bbe::kHid) && alloc(&m->h2, B * bbe::kHid) &&
                alloc(&m->h3, B * bbe::kHid) && alloc(&m->dz4, B * bbe::kOutP) &&
                alloc(&m->dz3, B * bbe::kHid) && alloc(&m->dz2, B * bbe::kHid) &&
-               alloc(&m->dz1, B * bbe::kHid);
+               alloc(&m->dz1, B * bbe::kHid) && alloc(&m->xf, B * bbe::kIn) &&
+               alloc(&m->loss_part, B / 16);
     // weight-gradient work tiles: 64 x 64 blocks of each layer
     std::vector<bbe::WgradTile> tiles;
     const int rows[4] = {bbe::kHid, bbe::kHid, bbe::kHid, bbe::kOut};
@@ -251,7 +258,7 @@ BBE_API int bbe_mlp_forward(const bbe_mlp* m, const uint16_t* x, const int32_t* 
                             void* stream) {
     if (!m || !x || !n_valid) return fail(BBE_EINVAL, "NULL argument");
     if (batch < 1) return fail(BBE_EINVAL, "batch must be >= 1");
-    bbe::MlpFwdArgs a = fwd_args(m, x, n_valid, batch);
+    bbe::MlpArgs a = fwd_args(m, x, n_valid, batch);
     a.probs = probs;
     a.entropy = entropy;
     a.logits = logits;
@@ -264,7 +271,7 @@ BBE_API int bbe_mlp_forward_hidden(const bbe_mlp* m, const uint16_t* x, const in
                                    int batch, uint16_t* hidden, float* logits, void* stream) {
     if (!m || !x || !n_valid || !hidden) return fail(BBE_EINVAL, "NULL argument");
     if (batch < 1) return fail(BBE_EINVAL, "batch must be >= 1");
-    bbe::MlpFwdArgs a = fwd_args(m, x, n_valid, batch);
+    bbe::MlpArgs a = fwd_args(m, x, n_valid, batch);
     const size_t layer = (size_t)batch * bbe::kHid;
     a.h1 = hidden;
     a.h2 = hidden + layer;
@@ -275,50 +282,68 @@ BBE_API int bbe_mlp_forward_hidden(const bbe_mlp* m, const uint16_t* x, const in
     return ok();
 }
 
-BBE_API int bbe_mlp_loss_grad(bbe_mlp* m, const uint16_t* x, const int32_t* n_valid,
-                              const float* target, int batch, float* loss, float* grad,
-                              void* stream) {
+namespace {
+
+// Forward, backward and weight gradients of a batch, into g (the batch is one
+// chunk) or into the chunks' partials; the loss into loss.
+hipError_t enqueue_gradients(bbe_mlp* m, const uint16_t* x, const int32_t* n_valid,
+                             const float* target, int batch, float* loss, float* g,
+                             hipStream_t s) {
+    bbe::MlpArgs f = fwd_args(m, x, n_valid, batch);
+    f.w2t = m->w2t;
+    f.w3t = m->w3t;
+    f.w4t = m->w4t;
+    f.target = target;
+    f.loss_part = m->loss_part;
+    f.xf = m->xf;
+    f.hf1 = m->h1;
+    f.hf2 = m->h2;
+    f.hf3 = m->h3;
+    f.df1 = m->dz1;
+    f.df2 = m->dz2;
+    f.df3 = m->dz3;
+    f.df4 = m->dz4;
+    hipError_t e = BBE_HIP(bbe::launch_mlp_train(f, s));
+    if (e != hipSuccess) return e;
+    bbe::MlpWgradArgs w;
+    w.B = batch;
+    w.n_parts = bbe::mlp_wgrad_parts(batch);
+    w.tiles = m->tiles;
+    w.layers[0] = {m->dz1, m->xf, bbe::kIn, bbe::kHid, g + bbe::kOffW1, g + bbe::kOffB1,
+                   bbe::kOffW1};
+    w.layers[1] = {m->dz2, m->h1, bbe::kHid, bbe::kHid, g + bbe::kOffW2, g + bbe::kOffB2,
+                   bbe::kOffW2};
+    w.layers[2] = {m->dz3, m->h2, bbe::kHid, bbe::kHid, g + bbe::kOffW3, g + bbe::kOffB3,
+                   bbe::kOffW3};
+    w.layers[3] = {m->dz4, m->h3, bbe::kHid, bbe::kOut, g + bbe::kOffW4, g + bbe::kOffB4,
+                   bbe::kOffW4};
+    w.part = m->wpart;
+    w.loss_part = m->loss_part;
+    w.n_loss = bbe::mlp_train_groups(batch);
+    w.loss = loss;
+    return bbe::launch_mlp_wgrad(w, m->n_tiles, s);
+}
+
+int check_training(const bbe_mlp* m, const uint16_t* x, const int32_t* n_valid,
+                   const float* target, int batch, const float* loss) {
     if (!m || !x || !n_valid || !target || !loss) return fail(BBE_EINVAL, "NULL argument");
     if (batch < 1 || batch > m->max_batch)
         return fail(BBE_EINVAL, "batch must be in 1..%d", m->max_batch);
+    return BBE_OK;
+}
+
+}  // namespace
+
+BBE_API int bbe_mlp_loss_grad(bbe_mlp* m, const uint16_t* x, const int32_t* n_valid,
+                              const float* target, int batch, float* loss, float* grad,
+                              void* stream) {
+    int rc = check_training(m, x, n_valid, target, batch, loss);
+    if (rc != BBE_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
     float* g = grad ? grad : m->grad;
-    hipError_t e = BBE_HIP(bbe::launch_fill_f32(loss, 0.0f, 1, s));
-    if (e == hipSuccess) e = bbe::launch_fill_f32(g, 0.0f, bbe::kNParams, s);
-    bbe::MlpFwdArgs f = fwd_args(m, x, n_valid, batch);
-    f.h1 = m->h1;
-    f.h2 = m->h2;
-    f.h3 = m->h3;
-    f.target = target;
-    f.dz = m->dz4;
-    f.loss = loss;
-    if (e == hipSuccess) e = bbe::launch_mlp_fwd(f, s);
-    bbe::MlpBwdArgs b;
-    b.B = batch;
-    b.dz4 = m->dz4;
-    b.w4t = m->w4t;
-    b.w3t = m->w3t;
-    b.w2t = m->w2t;
-    b.h1 = m->h1;
-    b.h2 = m->h2;
-    b.h3 = m->h3;
-    b.dz3 = m->dz3;
-    b.dz2 = m->dz2;
-    b.dz1 = m->dz1;
-    if (e == hipSuccess) e = bbe::launch_mlp_bwd_data(b, s);
-    bbe::MlpWgradArgs w;
-    w.B = batch;
-    w.tiles = m->tiles;
-    w.layers[0] = {m->dz1, bbe::kHid, x, bbe::kIn, bbe::kHid, g + bbe::kOffW1, g + bbe::kOffB1,
-                   bbe::kOffW1};
-    w.layers[1] = {m->dz2, bbe::kHid, m->h1, bbe::kHid, bbe::kHid, g + bbe::kOffW2,
-                   g + bbe::kOffB2, bbe::kOffW2};
-    w.layers[2] = {m->dz3, bbe::kHid, m->h2, bbe::kHid, bbe::kHid, g + bbe::kOffW3,
-                   g + bbe::kOffB3, bbe::kOffW3};
-    w.layers[3] = {m->dz4, bbe::kOutP, m->h3, bbe::kHid, bbe::kOut, g + bbe::kOffW4,
-                   g + bbe::kOffB4, bbe::kOffW4};
-    w.part = m->wpart;
-    if (e == hipSuccess) e = bbe::launch_mlp_wgrad(w, m->n_tiles, s);
+    hipError_t e = enqueue_gradients(m, x, n_valid, target, batch, loss, g, s);
+    const int parts = bbe::mlp_wgrad_parts(batch);
+    if (e == hipSuccess && parts > 1) e = bbe::launch_mlp_wreduce(m->wpart, parts, g, s);
     if (e != hipSuccess) return hip_fail(e, "launching the backward pass");
     return ok();
 }
@@ -336,9 +361,25 @@ BBE_API int bbe_mlp_adam_step(bbe_mlp* m, const float* grad, float lr, void* str
 BBE_API int bbe_mlp_train_step(bbe_mlp* m, const uint16_t* x, const int32_t* n_valid,
                                const float* target, int batch, float lr, float* loss,
                                void* stream) {
-    int rc = bbe_mlp_loss_grad(m, x, n_valid, target, batch, loss, nullptr, stream);
+    int rc = check_training(m, x, n_valid, target, batch, loss);
     if (rc != BBE_OK) return rc;
-    return bbe_mlp_adam_step(m, nullptr, lr, stream);
+    if (bbe::mlp_wgrad_parts(batch) == 1 || !std::isfinite(lr) || !(lr > 0.0f)) {
+        rc = bbe_mlp_loss_grad(m, x, n_valid, target, batch, loss, nullptr, stream);
+        if (rc != BBE_OK) return rc;
+        return bbe_mlp_adam_step(m, nullptr, lr, stream);
+    }
+    // the partial gradients are summed on the way into the step
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    hipError_t e = enqueue_gradients(m, x, n_valid, target, batch, loss, m->grad, s);
+    if (e != hipSuccess) return hip_fail(e, "launching the backward pass");
+    m->step += 1;
+    bbe::MlpAdamArgs a = adam_args(m, nullptr, lr);
+    a.part = m->wpart;
+    a.n_parts = bbe::mlp_wgrad_parts(batch);
+    a.grad_out = m->grad;
+    e = BBE_HIP(bbe::launch_mlp_adam(a, s));
+    if (e != hipSuccess) return hip_fail(e, "launching the Adam step");
+    return ok();
 }
 
 BBE_API int bbe_encode_states(const float* comp, const int32_t* n, const float* pos,

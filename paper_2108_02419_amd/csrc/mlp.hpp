@@ -27,34 +27,36 @@ constexpr int kOffB4 = kOffW4 + kOut * kHid;
 constexpr int kNParams = kOffB4 + kOut;
 static_assert(kNParams == 177940, "parameter count");
 
-struct MlpFwdArgs {
+// a thread's four parameters lie in one layer
+static_assert(kOffB1 % 4 == 0 && kOffW2 % 4 == 0 && kOffB2 % 4 == 0 && kOffW3 % 4 == 0 &&
+                  kOffB3 % 4 == 0 && kOffW4 % 4 == 0 && kOffB4 % 4 == 0 && kNParams % 4 == 0,
+              "layers in whole groups of four parameters");
+
+// Forward pass (and, for training, the gradients of the pre-activations).
+// Fragment order: see mlp_kernels.hip.
+struct MlpArgs {
     const uint16_t* x;        // [B][160] bf16
     const int32_t* n_valid;   // [B]
     int B;
-    const uint16_t *w1, *w2, *w3, *w4;  // bf16 [256][160], [256][256] x2, [32][256]
+    // bf16 weights in fragment order: [256][160], [256][256] x2, [32][256],
+    // and for training the transposes [256][32], [256][256] x2
+    const uint16_t *w1, *w2, *w3, *w4, *w4t, *w3t, *w2t;
     const float *b1, *b2, *b3, *b4;
-    uint16_t *h1, *h2, *h3;   // [B][256] bf16 or null
+    uint16_t *h1, *h2, *h3;   // [B][256] bf16 or null (inference)
     float* probs;             // [B][20] or null
     float* entropy;           // [B] or null
     float* logits;            // [B][32] or null
-    const float* target;      // [B][20] or null (training)
-    uint16_t* dz;             // [B][32] bf16 (training)
-    float* loss;              // [1] (training, accumulated)
+    // training
+    const float* target;      // [B][20]
     float inv_batch;
-};
-
-struct MlpBwdArgs {
-    int B;
-    const uint16_t* dz4;  // [B][32]
-    const uint16_t *w4t, *w3t, *w2t;  // [256][32], [256][256], [256][256]
-    const uint16_t *h1, *h2, *h3;
-    uint16_t *dz3, *dz2, *dz1;  // [B][256]
+    float* loss_part;         // [workgroups]
+    uint16_t *xf, *hf1, *hf2, *hf3;       // inputs of the layers, fragment order over the batch
+    uint16_t *df1, *df2, *df3, *df4;      // gradients of the pre-activations, the same
 };
 
 struct LayerGrad {
-    const uint16_t* dz;  // [B][dz_stride]
-    int dz_stride;
-    const uint16_t* h;   // [B][K] input of the layer
+    const uint16_t* dz;  // gradients of the outputs, fragment order over the batch
+    const uint16_t* h;   // inputs of the layer, the same
     int K;
     int n_rows;          // outputs of the layer
     float* gw;           // [n_rows][K]
@@ -71,17 +73,29 @@ struct WgradTile {
 
 struct MlpWgradArgs {
     int B;
+    int n_parts;  // mlp_wgrad_parts(B)
     LayerGrad layers[4];
     const WgradTile* tiles;
     // partial weight gradients, one packed parameter vector per chunk of
-    // kWgRows rows (needed when B > kWgRows); summed in chunk order
+    // kWgRows rows (used when B > kWgRows); summed in chunk order
     float* part;
+    const float* loss_part;  // [n_loss], summed into loss
+    int n_loss;
+    float* loss;
 };
+
+// Chunks (= partial gradients) of a batch.
+constexpr int mlp_wgrad_parts(int B) { return (B + kWgRows - 1) / kWgRows; }
 
 struct MlpAdamArgs {
     float* params;
     float *m, *v;
-    const float* grad;  // null: refresh the bf16 copies only
+    // the gradient: a vector, or n_parts partials to sum into grad_out; both
+    // null: refresh the bf16 copies only
+    const float* grad;
+    const float* part;
+    int n_parts;
+    float* grad_out;
     float lr, beta1, beta2, eps, inv_bc1, inv_bc2;
     uint16_t *w1, *w2, *w3, *w4, *w2t, *w3t, *w4t;
 };
@@ -99,11 +113,12 @@ struct EncodeArgs {
     float* target;           // [B][20] slot order (with probs_in)
 };
 
-hipError_t launch_mlp_fwd(const MlpFwdArgs& a, hipStream_t s);
-hipError_t launch_mlp_bwd_data(const MlpBwdArgs& a, hipStream_t s);
+hipError_t launch_mlp_fwd(const MlpArgs& a, hipStream_t s);
+hipError_t launch_mlp_train(const MlpArgs& a, hipStream_t s);
+int mlp_train_groups(int B);  // workgroups of launch_mlp_train
+hipError_t launch_mlp_wreduce(const float* part, int n_parts, float* grad, hipStream_t s);
 hipError_t launch_mlp_wgrad(const MlpWgradArgs& a, int n_tiles, hipStream_t s);
 hipError_t launch_mlp_adam(const MlpAdamArgs& a, hipStream_t s);
 hipError_t launch_encode(const EncodeArgs& a, hipStream_t s);
-hipError_t launch_fill_f32(float* p, float v, int n, hipStream_t s);
 
 }  // namespace bbe
