@@ -12,7 +12,8 @@ using namespace bbe_abi;
 struct bbe_bettors {
     uint32_t n = 0;
     uint32_t per_kind[4] = {0, 0, 0, 0};
-    uint8_t* kind = nullptr;  // device, grouped by kind
+    uint32_t window = 0;      // largest LinEx window
+    uint8_t* kind = nullptr;  // device, slices grouped by kind
     float* param = nullptr;
     uint32_t* id = nullptr;
 };
@@ -76,11 +77,15 @@ BBE_API int bbe_bettors_create(const uint8_t* kind, const float* param, int n_be
                 return fail(BBE_EINVAL, "bettor %d: unknown kind %d", b, (int)kind[b]);
         }
     }
-    // group by kind, keeping the caller's order within a kind
+    // slices of consecutive bettors, each grouped by kind, keeping the
+    // caller's order within a kind
     std::vector<uint32_t> order((size_t)n_bettors);
     for (int b = 0; b < n_bettors; ++b) order[(size_t)b] = (uint32_t)b;
     std::stable_sort(order.begin(), order.end(),
-                     [&](uint32_t x, uint32_t y) { return kind[x] < kind[y]; });
+                     [&](uint32_t x, uint32_t y) {
+                         const uint32_t sx = x / bbe::kViewSlice, sy = y / bbe::kViewSlice;
+                         return sx != sy ? sx < sy : kind[x] < kind[y];
+                     });
     std::vector<uint8_t> k((size_t)n_bettors);
     std::vector<float> p((size_t)n_bettors);
     for (size_t j = 0; j < order.size(); ++j) {
@@ -91,7 +96,10 @@ BBE_API int bbe_bettors_create(const uint8_t* kind, const float* param, int n_be
     bbe_bettors* b = new (std::nothrow) bbe_bettors();
     if (!b) return fail(BBE_ENOMEM, "out of host memory");
     b->n = (uint32_t)n_bettors;
-    for (int i = 0; i < n_bettors; ++i) b->per_kind[kind[i]] += 1;
+    for (int i = 0; i < n_bettors; ++i) {
+        b->per_kind[kind[i]] += 1;
+        if (kind[i] == BBE_BETTOR_LINEX) b->window = std::max(b->window, (uint32_t)param[i]);
+    }
     const size_t nb = (size_t)n_bettors;
     if (dev_alloc(&b->kind, nb) != hipSuccess ||
         dev_alloc(&b->param, nb * sizeof(float)) != hipSuccess ||
@@ -143,6 +151,7 @@ BBE_API int bbe_bettor_views(const bbe_bettors* b, const float* trace, uint32_t 
     a.param = b->param;
     a.id = b->id;
     a.n_bettors = b->n;
+    a.window = b->window;
     a.k0 = (uint32_t)seed;
     a.k1 = (uint32_t)(seed >> 32);
     a.views = views;

@@ -31,8 +31,10 @@ struct TraceArgs {
 enum : uint8_t { kZI = 0, kLW = 1, kUD = 2, kLinEx = 3 };
 
 // Views of a bettor population at trace rows first_row .. first_row +
-// n_eval - 1.  The population is stored grouped by kind (stable), so that
-// the waves of a launch run one rule each: slot j holds bettor id[j].
+// n_eval - 1.  The population is stored in slices of kViewSlice consecutive
+// bettors, each grouped by kind (stable), so that the waves of a launch run
+// one rule each and a workgroup's views lie together: slot j holds bettor
+// id[j].
 struct ViewArgs {
     const float* trace;  // [n_rows][n]
     int n;
@@ -40,20 +42,25 @@ struct ViewArgs {
     uint32_t t0;         // tick of trace row 0
     uint32_t first_row;
     uint32_t n_eval;
-    const uint8_t* kind;   // [n_bettors], grouped by kind
+    const uint8_t* kind;   // [n_bettors], slices grouped by kind
     const float* param;    // [n_bettors], same order
     const uint32_t* id;    // [n_bettors], caller's bettor index of each slot
     uint32_t n_bettors;
+    uint32_t window;       // largest LinEx window of the population (0: none)
+    uint32_t slices;       // slices per workgroup (set by the launcher)
+    uint32_t rows;         // trace rows per workgroup and chunk (set by the launcher)
     uint32_t k0, k1;       // ZI draws: Philox key
     uint8_t* views;        // [n_eval][n_bettors] by caller index, or null
     uint32_t* counts;      // [n_eval][n], or null; cleared by the launcher
 };
 
-constexpr int kViewBlock = 256;
+constexpr int kViewSlice = 1024;
 constexpr int kViewRowsPerBlock = 8;
 // rows of history staged in LDS for LinEx windows (longer windows read the
-// trace in global memory)
+// trace in global memory), and the windows settled once per row (longer ones
+// are scanned per bettor)
 constexpr int kViewWindow = 120;
+constexpr int kViewPicks = 256;
 
 hipError_t launch_race_trace(const TraceArgs& a, hipStream_t s);
 hipError_t launch_bettor_views(const ViewArgs& a, hipStream_t s);
