@@ -197,6 +197,11 @@ BBE_API int bbe_race_sim(const bbe_race* race, const bbe_state* state, uint32_t 
     if (a.steps && (e = BBE_HIP(bbe::launch_zero_u64(a.steps, 1, s))) != hipSuccess)
         return hip_fail(e, "zeroing step_count");
 
+    if (bbe::team_mc_fits(race->n, n_sims)) {
+        if ((e = BBE_HIP(bbe::launch_team_mc(a, s))) != hipSuccess)
+            return hip_fail(e, "launching race_mc_kernel");
+        return ok();
+    }
     const int block = bbe::mc_block_size();
     uint64_t need = ((uint64_t)n_sims + block - 1) / block;
     uint64_t resident = (uint64_t)bbe::mc_blocks_per_cu(race->n, race->pace.paced != 0) * device_cus();

@@ -52,6 +52,9 @@ int mc_blocks_per_cu(int n, bool paced);
 int mc_blocks_per_cu_paced(int n);
 hipError_t launch_race_mc_paced(const SimArgs& a, int grid, hipStream_t s);
 hipError_t launch_race_mc(const SimArgs& a, int grid, hipStream_t s);
+// Few simulations, a team of lanes each (team_kernels.hip), plain or paced.
+bool team_mc_fits(int n, uint32_t n_sims);
+hipError_t launch_team_mc(const SimArgs& a, hipStream_t s);
 hipError_t launch_race_prefix(const PrefixArgs& a, hipStream_t s);
 hipError_t launch_zero_u64(unsigned long long* p, int n, hipStream_t s);
 // Finish-order tallies over an orders matrix [n_sims][n] (see order_kernels.hip);

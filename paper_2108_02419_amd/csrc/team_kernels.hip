@@ -1,7 +1,8 @@
-// team_kernels.hip -- single simulations on gfx950: the race the bettors
-// watch (its trace, its next state) and the in-play states of a batch of
-// requests (paper Section 3: the race state is the vector of positions,
-// advanced tick by tick by Eq. 1).
+// team_kernels.hip -- single simulations and small Monte-Carlo runs on gfx950:
+// the race the bettors watch (its trace, its next state), the in-play states
+// of a batch of requests (paper Section 3: the race state is the vector of
+// positions, advanced tick by tick by Eq. 1), and dry-runs that are too few
+// to fill the chip with a simulation a lane.
 //
 // A team of lanes runs one simulation, lane c for competitor c, with no order
 // kept among them.  The Monte-Carlo kernels put a whole simulation in a lane
@@ -68,9 +69,10 @@ __device__ __forceinline__ TeamLane team_lane(const RaceConst& rc, const RacePac
 }
 
 // Ticks of every team of the wave from its tick t on, for as long as
-// before(t) -- asked before each tick -- and after(crossed, t) -- told
-// afterwards whether somebody reached the line, and the next tick -- both
-// hold for the team (they give the same answer in all its lanes).  A
+// before(t) -- asked before each tick -- and after(crossed, cr, t) -- told
+// afterwards whether somebody reached the line, whether this lane's
+// competitor did, and the next tick -- both hold for the team (they give the
+// same answer in all its lanes).  A competitor at NaN has left the race.  A
 // competitor that reaches the line keeps its position of before the tick.
 // J >= n (a multiple of 4): the competitors looked at.
 template <int G, int J, class Before, class After>
@@ -136,13 +138,13 @@ __device__ __forceinline__ void team_run(TeamLane& me, uint32_t c, uint32_t n, u
             me.d = cr ? me.d : dn;
             me.s = S;
             t += 1;
-            run = after(crossed, t);
+            run = after(crossed, cr, t);
         }
         i += 1;
     }
 }
 
-// Instance of team_run for the largest n of the wave.
+// Instance of team_run for the largest n of the wave (at most G).
 template <int G, class Before, class After>
 __device__ __forceinline__ void team_run_any(uint32_t n_max, TeamLane& me, uint32_t c,
                                              uint32_t n, uint32_t draws, uint32_t pairs, float L,
@@ -152,8 +154,9 @@ __device__ __forceinline__ void team_run_any(uint32_t n_max, TeamLane& me, uint3
     switch ((n_max + 3u) / 4u) {
 #define BBE_CASE(m)                                                                            \
     case m:                                                                                    \
-        team_run<G, 4 * m>(me, c, n, draws, pairs, L, t, sim, request, k0, k1, run, before,    \
-                           after);                                                             \
+        if constexpr (4 * m <= G)                                                              \
+            team_run<G, 4 * m>(me, c, n, draws, pairs, L, t, sim, request, k0, k1, run,        \
+                               before, after);                                                 \
         break;
         BBE_CASE(1) BBE_CASE(2) BBE_CASE(3) BBE_CASE(4) BBE_CASE(5)
 #undef BBE_CASE
@@ -181,7 +184,7 @@ __global__ void __launch_bounds__(64) race_prefix_kernel(const PrefixArgs a) {
             }
             return true;
         },
-        [&](bool crossed, uint32_t t) {
+        [&](bool crossed, bool, uint32_t t) {
             t_end = t;
             ok = !crossed;
             return !crossed;
@@ -205,7 +208,7 @@ __global__ void __launch_bounds__(64) race_trace_kernel(const TraceArgs a) {
     team_run_any<64>(
         n, me, c, n, draws, pairs, a.rc.L, a.t0, a.sim, a.request, a.k0, a.k1, true,
         [&](uint32_t) { return rows < a.max_rows; },
-        [&](bool crossed, uint32_t) {
+        [&](bool crossed, bool, uint32_t) {
             if (crossed) return false;
             if (c < n) a.trace[(size_t)rows * n + c] = me.d;
             rows += 1;
@@ -247,7 +250,7 @@ __global__ void __launch_bounds__(64)
             }
             return true;
         },
-        [&](bool crossed, uint32_t t) {
+        [&](bool crossed, bool, uint32_t t) {
             t_end = t;
             ok = !crossed;
             return !crossed;
@@ -260,10 +263,110 @@ __global__ void __launch_bounds__(64)
     }
 }
 
+// Monte-Carlo dry-runs, a team each (see launch_team_mc for when): finish
+// orders, win counts and competitor-steps as race_mc_kernel gives them.
+constexpr int kTeamMcBlock = 256;
+
+template <int G>
+__global__ void __launch_bounds__(kTeamMcBlock) team_mc_kernel(const SimArgs a) {
+    constexpr int kTeams = kTeamMcBlock / G;
+    __shared__ __attribute__((aligned(16))) char smem[kTeams * kTeamBytes<G>];
+    __shared__ uint32_t s_wins[kMaxN];
+    __shared__ unsigned long long s_steps;
+    const uint32_t c = threadIdx.x % G, n = (uint32_t)a.rc.n;
+    const uint32_t draws = lds_addr(smem) + (threadIdx.x / G) * kTeamBytes<G>;
+    const uint32_t pairs = draws + G * 32;
+    if (threadIdx.x < kMaxN) s_wins[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) s_steps = 0ull;
+    __syncthreads();
+    const uint32_t base = __lane_id() & ~(uint32_t)(G - 1);
+    const uint64_t team = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1) << base;
+    unsigned long long steps = 0ull;
+    // a wave's teams take neighbouring simulations and go on together
+    for (uint64_t first = ((uint64_t)blockIdx.x * kTeamMcBlock + (threadIdx.x & ~63u)) / G;
+         first < a.n_sims; first += (uint64_t)gridDim.x * kTeams) {
+        const uint64_t j = first + (threadIdx.x & 63u) / G;
+        const bool have = j < a.n_sims;
+        uint8_t* row = a.orders ? a.orders + (have ? j : 0) * n : nullptr;
+        TeamLane me = team_lane(a.rc, a.pace, a.d0, a.s0, a.id0, c, pairs);
+        uint32_t nfin = 0, ran = 0;
+        team_run_any<G>(
+            n, me, c, n, draws, pairs, a.rc.L, a.t0, a.sim_begin + (uint32_t)j, a.request, a.k0,
+            a.k1, have, [](uint32_t) { return true; },
+            [&](bool crossed, bool cr, uint32_t t) {
+                if (crossed) {
+                    // finishers of one tick by crossing fraction, then index
+                    const uint64_t who = __builtin_amdgcn_ballot_w64(cr) & team;
+                    uint32_t rank = nfin;
+                    if (who & (who - 1)) {
+                        const float f = (a.rc.L - me.d) / me.s;
+                        if (cr) lds_st(pairs + 8u * c, f);
+                        wave_fence();
+                        if (cr)
+                            for (uint64_t m = who; m; m &= m - 1) {
+                                const uint32_t o = (uint32_t)__builtin_ctzll(m) - base;
+                                const float fo = lds_ld<float>(pairs + 8u * o);
+                                rank += fo < f || (fo == f && o < c) ? 1u : 0u;
+                            }
+                        wave_fence();
+                    }
+                    if (cr) {
+                        if (rank == 0) atomicAdd(&s_wins[c], 1u);
+                        if (row) row[rank] = (uint8_t)c;
+                        ran = t - a.t0;
+                        me.d = parked();
+                    }
+                    nfin += (uint32_t)__popcll(who);
+                }
+                if (nfin < (uint32_t)a.stop_after && t - a.t0 < kTickLimit) return true;
+                if (c < n && me.d == me.d) ran = t - a.t0;
+                if (row && c >= nfin && c < n) row[c] = 0xFF;
+                return false;
+            });
+        steps += have ? ran : 0u;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) steps += __shfl_xor(steps, off, 64);
+    if ((threadIdx.x & 63) == 0 && steps) atomicAdd(&s_steps, steps);
+    __syncthreads();
+    if (a.wins && threadIdx.x < n && s_wins[threadIdx.x])
+        atomicAdd(&a.wins[threadIdx.x], (unsigned long long)s_wins[threadIdx.x]);
+    if (a.steps && threadIdx.x == 0 && s_steps) atomicAdd(a.steps, s_steps);
+}
+
 // ---------------------------------------------------------------- launchers
 
 hipError_t launch_race_prefix(const PrefixArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(race_prefix_kernel, dim3(1), dim3(64), 0, s, a);
+    return hipGetLastError();
+}
+
+// Whether n_sims dry-runs of n competitors end sooner with a team each than
+// with a lane each.  A lane each takes as long as one simulation does in a
+// lane, however few there are (until 4 waves a SIMD are full); teams take a
+// fraction of that, but of every wave they fill, so the line lies where their
+// waves begin to queue: at so many simulations per competitor for teams of 8,
+// 16 and 32 lanes.  Measured on both sides, full orders, us (team / lane):
+//   n = 5   1000: 119 / 235    32768: 176 / 238     49152: 233 / 241
+//   n = 13  1000: 179 / 600    32768: 494 / 612     49152: 705 / 612
+//   n = 20  1000: 201 / 940    24576: 821 / 947     32768: 1064 / 947
+// One competitor needs no look at the others: a lane each, 80 against 105.
+bool team_mc_fits(int n, uint32_t n_sims) {
+    if (n < 2) return false;
+    const uint32_t per = n <= 8 ? 7168u : n <= 16 ? 2560u : 1280u;
+    return n_sims <= per * (uint32_t)n;
+}
+
+hipError_t launch_team_mc(const SimArgs& a, hipStream_t s) {
+    const int n = a.rc.n;
+    const uint32_t lanes = n <= 8 ? 8 : n <= 16 ? 16 : 32;
+    const dim3 grid((unsigned)(((uint64_t)a.n_sims * lanes + kTeamMcBlock - 1) / kTeamMcBlock));
+    if (n <= 8)
+        hipLaunchKernelGGL(team_mc_kernel<8>, grid, dim3(kTeamMcBlock), 0, s, a);
+    else if (n <= 16)
+        hipLaunchKernelGGL(team_mc_kernel<16>, grid, dim3(kTeamMcBlock), 0, s, a);
+    else
+        hipLaunchKernelGGL(team_mc_kernel<32>, grid, dim3(kTeamMcBlock), 0, s, a);
     return hipGetLastError();
 }
 
