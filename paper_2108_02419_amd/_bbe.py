@@ -290,6 +290,15 @@ def _requests(specs):
     return arr, len(specs), keep
 
 
+def _rows(a, dtype):
+    """``a`` with contiguous rows at a non-negative stride (itself, if so)."""
+    a = np.asarray(a, dtype=dtype)
+    if a.ndim == 2 and a.strides[0] >= 0 and a.strides[1] == a.itemsize and \
+            a.flags.aligned and a.dtype.isnative:
+        return a
+    return np.ascontiguousarray(a)
+
+
 class BatchPlan:
     """A plan over uneven requests (``bbe_batch_plan_*``).  Outputs are CUDA
     tensors bound at creation: ``wins`` int64 [n_reqs, 20], optional
@@ -312,9 +321,11 @@ class BatchPlan:
 
     def set_states(self, tick, pos, prev, stream=None):
         """``bbe_batch_plan_set_states``: new start states for every request,
-        tick uint32 [B] and pos / prev float32 [B, m] (m >= each race's n)."""
-        pos = np.ascontiguousarray(pos, dtype=np.float32)
-        prev = np.ascontiguousarray(prev, dtype=np.float32)
+        tick uint32 [B] and pos / prev float32 [B, m] (m >= each race's n).
+        Rows need not follow each other: one state repeated with
+        ``np.broadcast_to`` is not copied, and is checked and uploaded once."""
+        pos = _rows(pos, np.float32)
+        prev = _rows(prev, np.float32)
         tick = np.ascontiguousarray(tick, dtype=np.uint32)
         B = tick.shape[0]
         if B != self.n_reqs or pos.shape != prev.shape or pos.ndim != 2 or pos.shape[0] != B:

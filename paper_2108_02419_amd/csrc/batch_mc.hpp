@@ -13,15 +13,17 @@
 namespace bbe {
 
 // Per-wave LDS: draw table [kMaxN][64] floats, parameter records, win
-// histogram, the request's start state in slot order (positions, previous
-// steps, competitor ids) so that it does not occupy registers, and the
-// byte table the ranking of several same-tick finishers uses.
+// histogram, the lanes' result rows, simulation indices, request ids and
+// start states (u32[64] each), the start state in slot order (positions,
+// previous steps, competitor ids) so that it does not occupy registers, and
+// the byte table the ranking of several same-tick finishers uses.
 constexpr uint32_t kWaveU = kMaxN * 256;
 constexpr uint32_t kWavePar = kMaxN * 32;
 constexpr uint32_t kWaveHist = 128;
+constexpr uint32_t kWaveLanes = 1024;
 constexpr uint32_t kWaveInit = kMaxN * 12;
 constexpr uint32_t kWaveIds = kMaxN * 64;  // finisher ids of a tick, u8[N][64]
-constexpr uint32_t kWaveBytes = kWaveU + kWavePar + kWaveHist + kWaveInit + kWaveIds;
+constexpr uint32_t kWaveBytes = kWaveU + kWavePar + kWaveHist + kWaveLanes + kWaveInit + kWaveIds;
 
 __device__ __forceinline__ unsigned long long wave_sum_u64b(unsigned long long v) {
 #pragma unroll
@@ -36,54 +38,90 @@ constexpr int batch_skip_step() {
     return N >= 6 ? 2 : 0;
 }
 
+// One work item.  The simulations of an item with kChunkLanes may belong to
+// several requests, all of the same race and stop_after.  They start from the
+// same state unless the states were changed since the items were made: a
+// generation then runs once for each state among its lanes.
+// What differs by lane is read from LDS where it is used, by the items of one
+// request too: a variant with scalar indices for those was 2% faster at 5
+// competitors and equal or up to 2% slower from 9 on (40000 requests of 100 or
+// 128 simulations), as it needed more registers around the generation.
 template <int N, bool kPaced>
-__device__ __forceinline__ void run_chunk(const ReqDesc& rq, const Chunk& ch, char* smem,
-                                          uint32_t wbase, int lane, uint32_t k0, uint32_t k1,
-                                          unsigned long long* wins_row,
-                                          unsigned long long& steps) {
+__device__ __forceinline__ void run_chunk(const BatchArgs& a, const Chunk& ch, char* smem,
+                                          uint32_t wbase, int lane, unsigned long long& steps) {
+    const ReqDesc& rq = a.reqs[ch.req];
+    const bool of_one = !(ch.n & kChunkLanes);
     const uint32_t ubase = lds_addr(smem) + wbase;
-    const uint32_t ibase = ubase + kWaveU + kWavePar + kWaveHist + kWaveInit;
     const uint32_t pbase = ubase + kWaveU;
-    uint32_t* hist = reinterpret_cast<uint32_t*>(smem + wbase + kWaveU + kWavePar);
-    float* d0 = reinterpret_cast<float*>(smem + wbase + kWaveU + kWavePar + kWaveHist);
+    const uint32_t hbase = pbase + kWavePar;
+    const uint32_t lbase = hbase + kWaveHist;
+    const uint32_t ibase = lbase + kWaveLanes + kWaveInit;
+    float* d0 = reinterpret_cast<float*>(smem + wbase + kWaveU + kWavePar + kWaveHist + kWaveLanes);
     float* s0 = d0 + kMaxN;
     uint8_t* id0 = reinterpret_cast<uint8_t*>(s0 + kMaxN);
     write_params<N>(pbase, rq.rc, lane);
     if constexpr (kPaced) write_pace<N>(pbase, rq.pace, lane);
-    if (lane < N) {
-        hist[lane] = 0u;
-        d0[lane] = rq.d0[lane];
-        s0[lane] = rq.s0[lane];
-        id0[lane] = rq.id0[lane];
-    }
+    if (lane < N) lds_st<uint32_t>(hbase + 4u * lane, 0u);
     const StepBounds sb{rq.rc.step_cap, rq.rc.reach2, rq.rc.reach8};
     for (uint32_t g = 0; g < ch.count; g += 64) {
-        const bool live = g + lane < ch.count;
-        const uint32_t sim0 = rq.sim_begin + ch.first + g;
-        // re-read the start state from LDS each generation rather than
-        // keeping 3N registers live across the loop
-        __asm__ volatile("" ::: "memory");
-        run_generation<N, kPaced ? kPaceTable : kPaceOff, batch_skip_step<N>()>(
-            ubase, ibase, pbase, rq.rc.L, sb, d0, s0, id0, rq.t0, live, sim0, rq.request, k0,
-            k1, rq.stop_after, kNoRow, hist, steps);
+        const bool live = g + lane_here() < ch.count;
+        {
+            const uint32_t i = ch.first + (live ? g + lane_here() : 0u);
+            const PackLane pl = of_one ? PackLane{ch.req, rq.sim_begin + i} : a.lanes[i];
+            const uint32_t at = lbase + 4u * lane_here();
+            lds_st<uint32_t>(at, pl.row);
+            lds_st<uint32_t>(at + 256u, pl.sim);
+            lds_st<uint32_t>(at + 512u, a.reqs[pl.row].request);
+            lds_st<uint32_t>(at + 768u, a.state_of[pl.row]);
+        }
+        uint64_t todo = __builtin_amdgcn_ballot_w64(live);
+        while (todo) {
+            const uint32_t state = __builtin_amdgcn_readfirstlane(
+                lds_ld<uint32_t>(lbase + 768u + 4u * (uint32_t)__builtin_ctzll(todo)));
+            const bool mine = ((todo >> lane_here()) & 1ull) &&
+                              lds_ld<uint32_t>(lbase + 768u + 4u * lane_here()) == state;
+            todo &= ~__builtin_amdgcn_ballot_w64(mine);
+            const StartState& st = a.states[state];
+            if (lane < N) {
+                d0[lane] = st.d0[lane];
+                s0[lane] = st.s0[lane];
+                id0[lane] = st.id0[lane];
+            }
+            // re-read the start state from LDS each time rather than keeping
+            // 3N registers live across the loop
+            __asm__ volatile("" ::: "memory");
+            run_generation<N, kPaced ? kPaceTable : kPaceOff, batch_skip_step<N>()>(
+                ubase, ibase, pbase, rq.rc.L, sb, d0, s0, id0, st.t0, mine,
+                [&](uint32_t l) { return lds_ld<uint32_t>(lbase + 256u + 4u * l); },
+                [&](uint32_t l) { return lds_ld<uint32_t>(lbase + 512u + 4u * l); }, a.k0, a.k1,
+                rq.stop_after, kNoRow,
+                [&](uint32_t c) {
+                    if (of_one) {
+                        atomicAdd(reinterpret_cast<uint32_t*>(smem + wbase + kWaveU + kWavePar) +
+                                      c,
+                                  1u);
+                    } else {
+                        const uint32_t row = lds_ld<uint32_t>(lbase + 4u * lane_here());
+                        atomicAdd(&a.wins[(size_t)row * kMaxN + c], 1ull);
+                    }
+                },
+                steps);
+        }
     }
-    if (lane < N) {
-        uint32_t w = hist[lane];
-        if (w) atomicAdd(&wins_row[lane], (unsigned long long)w);
+    if (of_one && lane < N) {
+        const uint32_t w = lds_ld<uint32_t>(hbase + 4u * lane);
+        if (w) atomicAdd(&a.wins[(size_t)ch.req * kMaxN + lane], (unsigned long long)w);
     }
 }
 
 // Runs a work item with the template instance of its competitor count (a
 // wave-uniform switch on n).
 template <bool kPaced, int... I>
-__device__ __forceinline__ void run_chunk_any(int n, const ReqDesc& rq, const Chunk& ch,
-                                              char* smem, uint32_t wbase, int lane, uint32_t k0,
-                                              uint32_t k1, unsigned long long* wins_row,
+__device__ __forceinline__ void run_chunk_any(int n, const BatchArgs& a, const Chunk& ch,
+                                              char* smem, uint32_t wbase, int lane,
                                               unsigned long long& steps,
                                               std::integer_sequence<int, I...>) {
-    (void)((n == I + 1 ? (run_chunk<I + 1, kPaced>(rq, ch, smem, wbase, lane, k0, k1, wins_row,
-                                                    steps),
-                          true)
+    (void)((n == I + 1 ? (run_chunk<I + 1, kPaced>(a, ch, smem, wbase, lane, steps), true)
                        : false) ||
            ...);
 }
@@ -109,9 +147,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
         ci = __builtin_amdgcn_readfirstlane(ci);
         if (ci >= a.n_chunks) break;
         const Chunk ch = a.chunks[ci];
-        const int n = (int)__builtin_amdgcn_readfirstlane(ch.n);
-        run_chunk_any<kPaced>(n, a.reqs[ch.req], ch, smem, wbase, lane, a.k0, a.k1,
-                              a.wins + (size_t)ch.req * kMaxN, steps,
+        const int n = (int)(__builtin_amdgcn_readfirstlane(ch.n) & ~kChunkLanes);
+        run_chunk_any<kPaced>(n, a, ch, smem, wbase, lane, steps,
                               std::make_integer_sequence<int, kMaxN>{});
     }
     steps = wave_sum_u64b(steps);

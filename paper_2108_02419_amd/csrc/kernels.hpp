@@ -70,27 +70,40 @@ hipError_t launch_win_probs(const unsigned long long* wins, int n_rows, int n, i
 
 namespace bbe {
 
-// One request of a batch: a race, an initial state in slot order and a
-// range of simulations of stream (seed, request).  Read by whole waves
-// (uniform loads).
-struct alignas(16) ReqDesc {
-    RaceConst rc;
+// A start state in slot order.
+struct StartState {
     float d0[kMaxN];
     float s0[kMaxN];
     uint8_t id0[kMaxN];
     uint32_t t0;
+};
+
+// One request of a batch: a race and a range of simulations of stream (seed,
+// request).  Read by whole waves (uniform loads).
+struct alignas(16) ReqDesc {
+    RaceConst rc;
     uint32_t request;
     uint32_t sim_begin;
     uint32_t n_sims;
     int stop_after;
-    // in-play state generation only: simulation index and leader target
-    uint32_t prefix_sim;
+    RacePace pace;
+};
+
+// One in-play state to generate: simulation `sim` of stream (seed, request)
+// of a race, from a state until its leader reaches the target.
+struct alignas(16) PrefixDesc {
+    RaceConst rc;
+    StartState st;
+    uint32_t request;
+    uint32_t sim;
     float target;
     RacePace pace;
 };
 
 // A work item of the persistent kernel: simulations [first, first + count)
-// of request `req` (count <= 64 * generations per chunk).
+// of request `req` (count <= 64 * generations per chunk), or with kChunkLanes
+// in `n` entries [first, first + count) of the lane table.
+constexpr uint32_t kChunkLanes = 0x100u;
 struct Chunk {
     uint32_t req;
     uint32_t first;
@@ -98,11 +111,20 @@ struct Chunk {
     uint32_t n;
 };
 
+// An entry of the lane table: one simulation.
+struct PackLane {
+    uint32_t row;  // its request
+    uint32_t sim;  // its index
+};
+
 // One launch serves the work items chunks[0 .. n_chunks) of every
 // competitor count (chunk.n selects the template instance).
 struct BatchArgs {
     const ReqDesc* reqs;
     const Chunk* chunks;
+    const uint32_t* state_of;   // [n_reqs]: each request's entry of `states`
+    const StartState* states;
+    const PackLane* lanes;      // of the items with kChunkLanes
     uint32_t n_chunks;
     uint32_t* queue;            // the launch's work-queue head, zeroed before launch
     unsigned long long* wins;   // [n_reqs][kMaxN], zeroed before launch
@@ -121,7 +143,7 @@ int batch_blocks_per_cu_paced(int waves_per_block);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int n, hipStream_t s);
 hipError_t launch_batch_probs(const unsigned long long* wins, const ReqDesc* reqs, int n_reqs,
                               double* probs, hipStream_t s);
-hipError_t launch_prefix_batch(const ReqDesc* reqs, int n_reqs, uint32_t k0, uint32_t k1,
+hipError_t launch_prefix_batch(const PrefixDesc* reqs, int n_reqs, uint32_t k0, uint32_t k1,
                                uint32_t* tick_out, float* pos_out, float* prev_out,
                                hipStream_t s);
 

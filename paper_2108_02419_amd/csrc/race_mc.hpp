@@ -114,10 +114,12 @@ __global__ void __launch_bounds__(kBlock)
         // re-read the start state from LDS each generation rather than
         // keeping it live (in registers) across the loop
         __asm__ volatile("" ::: "memory");
+        const uint32_t sim0 = a.sim_begin + (uint32_t)first;
         run_generation<N, kPaced ? kPaceTable : kPaceOff, mc_skip_step<N>()>(
             ubase, ibase, pbase, L, sb, s_d0, s_s0, s_id0, a.t0, live,
-            a.sim_begin + (uint32_t)first, a.request, a.k0, a.k1, a.stop_after,
-            a.orders ? lds_addr(otab) : kNoRow, s_wins, steps);
+            [&](uint32_t l) { return sim0 + l; }, [&](uint32_t) { return a.request; }, a.k0, a.k1,
+            a.stop_after, a.orders ? lds_addr(otab) : kNoRow,
+            [&](uint32_t c) { atomicAdd(&s_wins[c], 1u); }, steps);
         if (a.orders) {
             // the wave's LDS operations complete in order; keep the compiler
             // from moving the table's reads above the lanes' writes (and the

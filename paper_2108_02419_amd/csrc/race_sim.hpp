@@ -281,11 +281,10 @@ __device__ __forceinline__ uint32_t slots_tick(Slots<N>& sl, uint32_t ucol,
 // ucol + 256*j -- and its slot is parked.  The entries are then picked in
 // (fraction, index) order by a selection over those c entries, so the work
 // grows with c^2 for the few finishers of a tick rather than with c*N.
-template <int N>
+template <int N, class Win>
 __device__ __forceinline__ int slots_rank_park(Slots<N>& sl, uint32_t cross, bool rank, float L,
-                                               uint32_t ucol, uint32_t icol,
-                                               uint32_t pbase, int nfin, uint32_t* hist,
-                                               uint32_t row) {
+                                               uint32_t ucol, uint32_t icol, uint32_t pbase,
+                                               int nfin, const Win& win, uint32_t row) {
     const int c = __builtin_popcount(cross);
 #pragma unroll
     for (int k = 0; k < N; ++k)
@@ -315,7 +314,7 @@ __device__ __forceinline__ int slots_rank_park(Slots<N>& sl, uint32_t cross, boo
         }
         used |= 1u << bj;  // c - r > 0 entries are unused, so bj >= 0
         const int rr = nfin + r;
-        if (rr == 0) atomicAdd(&hist[bid], 1u);
+        if (rr == 0) win(bid);
         if (row != kNoRow) lds_st<uint8_t>(row + rr, (uint8_t)bid);
     }
     return c;
@@ -657,10 +656,10 @@ __device__ __forceinline__ void slots_cross_all(Slots<N>& sl, float L, uint32_t&
 // slots_rank_park does.  The crossing fraction of competitor c goes to its own
 // place of the draw table, where slots_tick_plain left its start-of-tick
 // position.
-template <int N, int A>
+template <int N, int A, class Win>
 __device__ __forceinline__ int slots_rank(const Slots<N>& sl, uint32_t cross, uint32_t kset,
                                           bool rank, float L, uint32_t ucol, uint32_t icol,
-                                          uint32_t pbase, int nfin, uint32_t* hist, uint32_t row) {
+                                          uint32_t pbase, int nfin, const Win& win, uint32_t row) {
     const int c = __builtin_popcount(cross);
 #pragma unroll
     for (int k = 0; k < A; ++k)
@@ -693,7 +692,7 @@ __device__ __forceinline__ int slots_rank(const Slots<N>& sl, uint32_t cross, ui
         }
         used |= 1u << bj;  // c - r > 0 entries are unused, so bj >= 0
         const int rr = nfin + r;
-        if (rr == 0) atomicAdd(&hist[bid], 1u);
+        if (rr == 0) win(bid);
         if (row != kNoRow) lds_st<uint8_t>(row + rr, (uint8_t)bid);
     }
     return c;
@@ -715,24 +714,26 @@ __device__ __forceinline__ Outcome run_phases(F& f) {
 
 // One generation: up to 64 simulations of one race from one state, one per
 // lane, in lockstep from tick t0.  `live` marks the lanes that hold a
-// simulation (lane l: index sim0 + l); `rows` (or kNoRow) is the LDS table of
-// their finish orders, N bytes a lane; `ubase` and `ibase` locate the wave's draw and finisher-id tables.
+// simulation; sim_of(lane) and request_of(lane) are its index and its request
+// id; `rows` (or kNoRow) is the LDS table of their finish orders, N bytes a
+// lane; `ubase` and `ibase` locate the wave's draw and finisher-id tables.
 // Lanes whose simulation has ended keep stepping with the others (their
 // results are no longer recorded), so the tick needs no divergent branch.
-// Winners go to the LDS histogram `hist`; competitor-steps add to `steps`.
+// win(c) is told each simulation's winner; competitor-steps add to `steps`.
 // kSkipStep > 0 stops stepping and sorting the top slots once they are
 // parked in every lane, kSkipStep slots at a time (a copy of the tick per
 // active count): late in a generation most lanes have parked most of their
 // competitors.
-template <int N, Pace kPace = kPaceOff, int kSkipStep = 0>
+template <int N, Pace kPace, int kSkipStep, class Sim, class Request, class Win>
 __device__ __forceinline__ void run_generation(uint32_t ubase, uint32_t ibase, uint32_t pbase,
                                                float L, const StepBounds& sb,
                                                const float* __restrict__ d0,
                                                const float* __restrict__ s0,
                                                const uint8_t* __restrict__ id0, uint32_t t0,
-                                               bool live, uint32_t sim0, uint32_t request,
+                                               bool live, const Sim& sim_of,
+                                               const Request& request_of,
                                                uint32_t k0, uint32_t k1, int stop_after,
-                                               uint32_t rows, uint32_t* hist,
+                                               uint32_t rows, const Win& win,
                                                unsigned long long& steps) {
     Slots<N> sl;
     slots_reset<N>(sl, d0, s0, id0, pbase);
@@ -761,7 +762,8 @@ __device__ __forceinline__ void run_generation(uint32_t ubase, uint32_t ibase, u
     auto open_run = [&]() {
         // what depends on the simulation index only is computed once per run
         // of open ticks, and not kept across the other ticks
-        const uint32_t sim = sim0 + lane_here();
+        const uint32_t lane = lane_here();
+        const uint32_t sim = sim_of(lane), request = request_of(lane);
         float gap[N];
         bool tie = slots_gaps<N, N>(sl, gap);
         int left = t - t0 < kTickLimit - 16u ? open_ticks<N>(sl, L, sb) : 0;
@@ -797,8 +799,8 @@ __device__ __forceinline__ void run_generation(uint32_t ubase, uint32_t ibase, u
             if (!__builtin_amdgcn_ballot_w64(live)) return kEnded;
             t = __builtin_amdgcn_readfirstlane(t);  // the wave's: the compiler cannot tell
             const uint32_t lane = lane_here(), ucol = ubase + 4u * lane;
-            slots_tick_plain<N, kPace, A, true>(sl, gap, ucol, pbase, t, sim0 + lane, request,
-                                                k0, k1);
+            slots_tick_plain<N, kPace, A, true>(sl, gap, ucol, pbase, t, sim_of(lane),
+                                                request_of(lane), k0, k1);
             slots_sort<N, A>(sl);
             uint32_t cross = 0u, kset = 0u;
             slots_cross_all<N, 0, A>(sl, L, cross, kset);
@@ -806,7 +808,7 @@ __device__ __forceinline__ void run_generation(uint32_t ubase, uint32_t ibase, u
             int k = 0;
             if (kset)
                 k = slots_rank<N, A>(sl, cross, kset, live && cross, L, ucol,
-                                     ibase + lane, pbase, nfin, hist, row_of(lane));
+                                     ibase + lane, pbase, nfin, win, row_of(lane));
             end_tick(k);
             t += 1;
             if (kset && parked_below()) return kParked;
@@ -825,11 +827,12 @@ __device__ __forceinline__ void run_generation(uint32_t ubase, uint32_t ibase, u
             t = __builtin_amdgcn_readfirstlane(t);
             const uint32_t lane = lane_here(), ucol = ubase + 4u * lane;
             const uint32_t cross =
-                slots_tick<N, kPace>(sl, ucol, pbase, L, t, sim0 + lane, request, k0, k1);
+                slots_tick<N, kPace>(sl, ucol, pbase, L, t, sim_of(lane), request_of(lane), k0,
+                                     k1);
             int k = 0;
             if (__builtin_amdgcn_ballot_w64(cross != 0u))
                 k = slots_rank_park<N>(sl, cross, live && cross, L, ucol, ibase + lane, pbase,
-                                       nfin, hist, row_of(lane));
+                                       nfin, win, row_of(lane));
             end_tick(k);
             t += 1;
             slots_restore<N>(sl);
