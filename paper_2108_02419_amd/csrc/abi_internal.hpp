@@ -158,15 +158,12 @@ inline void to_slot_order(int n, const float* d, const float* s, float* d_out, f
     }
 }
 
-// Validates a state and writes it in slot order (state == NULL: start of
-// race, every competitor at 0, ordered by index).
-inline int check_state(int n, float L, const bbe_state* st, float* d0, float* s0, uint8_t* id0,
-                       uint32_t* t0) {
-    float d[BBE_MAX_COMPETITORS], s[BBE_MAX_COMPETITORS];
+// Validates a state and writes it in competitor order (state == NULL: start of
+// race, every competitor at 0).
+inline int check_values(int n, float L, const bbe_state* st, float* d, float* s, uint32_t* t0) {
     if (!st) {
         for (int c = 0; c < n; ++c) d[c] = s[c] = 0.0f;
         *t0 = 0;
-        to_slot_order(n, d, s, d0, s0, id0);
         return BBE_OK;
     }
     if (st->tick > 0xFFFFFFFFu - BBE_TICK_LIMIT)
@@ -182,8 +179,16 @@ inline int check_state(int n, float L, const bbe_state* st, float* d0, float* s0
         s[c] = q;
     }
     *t0 = st->tick;
-    to_slot_order(n, d, s, d0, s0, id0);
     return BBE_OK;
+}
+
+// The same, written in slot order.
+inline int check_state(int n, float L, const bbe_state* st, float* d0, float* s0, uint8_t* id0,
+                       uint32_t* t0) {
+    float d[BBE_MAX_COMPETITORS], s[BBE_MAX_COMPETITORS];
+    const int rc = check_values(n, L, st, d, s, t0);
+    if (rc == BBE_OK) to_slot_order(n, d, s, d0, s0, id0);
+    return rc;
 }
 
 inline int check_state(const bbe_race* r, const bbe_state* st, float* d0, float* s0, uint8_t* id0,

@@ -89,16 +89,20 @@ struct alignas(16) ReqDesc {
     RacePace pace;
 };
 
-// One in-play state to generate: simulation `sim` of stream (seed, request)
-// of a race, from a state until its leader reaches the target.
-struct alignas(16) PrefixDesc {
-    RaceConst rc;
-    StartState st;
+// In-play states to generate, a record of 32-bit words each: this head, then
+// elo, espan16, alpha, beta and theta of the n competitors, then gamma and tau
+// (kPrefixPaced), then positions and previous steps in competitor order
+// (kPrefixState; without, the race is at its start).
+struct PrefixHead {
+    uint32_t n;  // and the flags
     uint32_t request;
     uint32_t sim;
+    uint32_t t0;
     float target;
-    RacePace pace;
+    float L;
 };
+constexpr uint32_t kPrefixPaced = 0x100u, kPrefixState = 0x200u;
+constexpr uint32_t kPrefixWords = sizeof(PrefixHead) / 4 + 9 * kMaxN;  // of the largest record
 
 // A work item of the persistent kernel: simulations [first, first + count)
 // of request `req` (count <= 64 * generations per chunk), or with kChunkLanes
@@ -143,7 +147,8 @@ int batch_blocks_per_cu_paced(int waves_per_block);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int n, hipStream_t s);
 hipError_t launch_batch_probs(const unsigned long long* wins, const ReqDesc* reqs, int n_reqs,
                               double* probs, hipStream_t s);
-hipError_t launch_prefix_batch(const PrefixDesc* reqs, int n_reqs, uint32_t k0, uint32_t k1,
+// Record i begins at records[at[i]], or without `at` at records[kPrefixWords * i].
+hipError_t launch_prefix_batch(const uint32_t* records, const uint64_t* at, int n_reqs, uint32_t k0, uint32_t k1,
                                uint32_t* tick_out, float* pos_out, float* prev_out,
                                hipStream_t s);
 

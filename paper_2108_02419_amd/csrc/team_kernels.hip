@@ -217,12 +217,12 @@ __global__ void __launch_bounds__(64) race_trace_kernel(const TraceArgs a) {
     if (c == 0) *a.rows_out = rows;
 }
 
-// In-play states for a batch: team i advances simulation `sim` of
-// request i until its leader reaches the target.
+// In-play states for a batch: team i advances the simulation of record i until
+// its leader reaches the target.
 __global__ void __launch_bounds__(64)
-    prefix_batch_kernel(const PrefixDesc* __restrict__ reqs, int n_reqs, uint32_t k0, uint32_t k1,
-                        uint32_t* __restrict__ tick_out, float* __restrict__ pos_out,
-                        float* __restrict__ prev_out) {
+    prefix_batch_kernel(const uint32_t* __restrict__ records, const uint64_t* __restrict__ at,
+                        int n_reqs, uint32_t k0, uint32_t k1, uint32_t* __restrict__ tick_out,
+                        float* __restrict__ pos_out, float* __restrict__ prev_out) {
     constexpr int G = 32;
     __shared__ __attribute__((aligned(16))) char smem[2 * kTeamBytes<G>];
     const uint32_t half = threadIdx.x / G, c = threadIdx.x % G;
@@ -230,18 +230,36 @@ __global__ void __launch_bounds__(64)
     const int i = 2 * (int)blockIdx.x + (int)half;
     const bool have = i < n_reqs;
     // an odd batch's last half-wave idles through its neighbour's race
-    const PrefixDesc& rq = reqs[have ? i : n_reqs - 1];
-    const uint32_t n = (uint32_t)rq.rc.n;
+    const int mine = have ? i : n_reqs - 1;
+    const uint32_t* w = records + (at ? (size_t)at[mine] : (size_t)mine * kPrefixWords);
+    PrefixHead rq;
+    __builtin_memcpy(&rq, w, sizeof rq);
+    w += sizeof rq / 4;
+    const uint32_t n = rq.n & 0xFFu;
     const uint32_t n_max =
         max((uint32_t)__builtin_amdgcn_readlane(n, 0), (uint32_t)__builtin_amdgcn_readlane(n, G));
-    TeamLane me = team_lane(rq.rc, rq.pace, rq.st.d0, rq.st.s0, rq.st.id0, c, pairs);
+    TeamLane me;
+    if (c < n) {
+        const float* v = reinterpret_cast<const float*>(w) + c;
+        me = {v[0], v[n], v[2 * n], v[3 * n], v[4 * n], 0.0f, 0.0f, 0.0f, 0.0f};
+        v += 5 * n;
+        if (rq.n & kPrefixPaced) {
+            me.gamma = v[0];
+            me.tau = v[n];
+            v += 2 * n;
+        }
+        if (rq.n & kPrefixState) {
+            me.d = v[0];
+            me.s = v[n];
+        }
+    }
     const uint64_t team = 0xFFFFFFFFull << (half * G);
     const float target = rq.target;
-    const uint32_t t0 = rq.st.t0;
+    const uint32_t t0 = rq.t0;
     uint32_t t_end = t0;
     bool ok = true;
     team_run_any<G>(
-        n_max, me, c, n, draws, pairs, rq.rc.L, t0, rq.sim, rq.request, k0, k1, have,
+        n_max, me, c, n, draws, pairs, rq.L, t0, rq.sim, rq.request, k0, k1, have,
         [&](uint32_t t) {
             if (__builtin_amdgcn_ballot_w64(me.d >= target) & team) return false;
             if (t - t0 >= kTickLimit) {
@@ -375,12 +393,12 @@ hipError_t launch_race_trace(const TraceArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_prefix_batch(const PrefixDesc* reqs, int n_reqs, uint32_t k0, uint32_t k1,
+hipError_t launch_prefix_batch(const uint32_t* records, const uint64_t* at, int n_reqs, uint32_t k0, uint32_t k1,
                                uint32_t* tick_out, float* pos_out, float* prev_out,
                                hipStream_t s) {
     if (n_reqs <= 0) return hipSuccess;
     hipLaunchKernelGGL(prefix_batch_kernel, dim3((unsigned)(((long)n_reqs + 1) / 2)), dim3(64), 0,
-                       s, reqs, n_reqs, k0, k1, tick_out, pos_out, prev_out);
+                       s, records, at, n_reqs, k0, k1, tick_out, pos_out, prev_out);
     return hipGetLastError();
 }
 
