@@ -322,7 +322,7 @@ struct bbe_batch_plan {
     unsigned long long* wins = nullptr;
     double* probs = nullptr;
     unsigned long long* steps = nullptr;
-    Shape shape{4, 64, 1};
+    Shape shape{1, 64, 1};
     int item_sims = 64;  // simulations per work item in use (>= shape.sims_per_item)
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;
@@ -382,10 +382,23 @@ hipError_t enqueue(bbe_batch_plan* p, hipStream_t s) {
     return hipSuccess;
 }
 
-// Work items of a batch: ceil(n_sims / 64) generations per request.
+// Generations of a batch: ceil(n_sims / 64) per request.
 uint64_t generation_count(const std::vector<bbe::ReqDesc>& reqs) {
     uint64_t g = 0;
     for (const bbe::ReqDesc& r : reqs) g += (r.n_sims + 63u) / 64u;
+    return g;
+}
+
+// The same as build_work makes them, with shared ones counted once.
+uint64_t shared_generation_count(const std::vector<bbe::ReqDesc>& reqs,
+                                 const std::vector<uint32_t>& together) {
+    std::vector<uint64_t> over(reqs.size());
+    uint64_t g = 0;
+    for (size_t r = 0; r < reqs.size(); ++r) {
+        g += reqs[r].n_sims / 64u;
+        over[together[r]] += reqs[r].n_sims % 64u;
+    }
+    for (uint64_t o : over) g += (o + 63u) / 64u;
     return g;
 }
 
@@ -449,21 +462,22 @@ void destroy(bbe_batch_plan* p) {
     delete p;
 }
 
-// A request's descriptor and its start state (the bytes of both are set
-// throughout, so that equal ones compare equal).
-int fill_desc(const bbe_request& q, int idx, bbe::ReqDesc& d, bbe::StartState& st) {
-    if (!q.race) return fail(BBE_EINVAL, "request %d: race is NULL", idx);
+// A request's descriptor (its bytes are set throughout, so that equal ones
+// compare equal).
+void fill_desc(const bbe_request& q, bbe::ReqDesc& d) {
     std::memset(&d, 0, sizeof d);
-    std::memset(&st, 0, sizeof st);
     d.rc = q.race->rc;
     d.pace = q.race->pace;
-    int rc = check_state(q.race, q.state, st.d0, st.s0, st.id0, &st.t0);
-    if (rc != BBE_OK) return fail(rc, "request %d: %s", idx, g_err.c_str());
     d.request = q.request;
     d.sim_begin = q.sim_begin;
     d.n_sims = q.n_sims;
     d.stop_after = q.stop_after == 0 ? q.race->n : q.stop_after;
-    return BBE_OK;
+}
+
+// Whether two states are given by the same arrays.
+bool same_arrays(const bbe_state* a, const bbe_state* b) {
+    if (!a || !b) return a == b;
+    return a->tick == b->tick && a->pos == b->pos && a->prev_step == b->prev_step;
 }
 
 }  // namespace
@@ -485,8 +499,19 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
     Distinct<Together> groups((size_t)n_reqs);
     for (int i = 0; i < n_reqs; ++i) {
         const bbe_request& q = reqs[i];
-        bbe::StartState st;
-        int rc = fill_desc(q, i, p->host_reqs[i], st);
+        // a row of requests of one race from one state is looked at once
+        const bool again = i > 0 && q.race == reqs[i - 1].race;
+        int rc = BBE_OK;
+        if (again && same_arrays(q.state, reqs[i - 1].state)) {
+            state_of[i] = state_of[i - 1];
+        } else {
+            bbe::StartState st;
+            std::memset(&st, 0, sizeof st);
+            rc = q.race ? check_state(q.race, q.state, st.d0, st.s0, st.id0, &st.t0)
+                        : fail(BBE_EINVAL, "request %d: race is NULL", i);
+            if (rc == BBE_OK) state_of[i] = states.number(st);
+            else if (q.race) rc = fail(rc, "request %d: %s", i, g_err.c_str());
+        }
         if (rc != BBE_OK) {
             destroy(p);
             return rc;
@@ -504,8 +529,13 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
             return fail(BBE_EINVAL, "request %d: stop_after = %d outside 0..%d", i,
                         q.stop_after, q.race->n);
         }
-        state_of[i] = states.number(st);
-        const bbe::ReqDesc& d = p->host_reqs[i];
+        bbe::ReqDesc& d = p->host_reqs[i];
+        fill_desc(q, d);
+        if (again && state_of[i] == state_of[i - 1] &&
+            d.stop_after == p->host_reqs[i - 1].stop_after) {
+            p->together[i] = p->together[i - 1];
+            continue;
+        }
         Together t;
         std::memset(&t, 0, sizeof t);
         t.rc = d.rc;
@@ -529,11 +559,10 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
         destroy(p);
         return fail(BBE_ENOMEM, "device allocation of the request table failed");
     }
-    std::vector<char> table(req_bytes + p->states_used);
-    std::memcpy(table.data(), p->host_reqs.data(), req_bytes);
-    std::memcpy(table.data() + req_bytes, p->host_states.data(), p->states_used);
-    if ((e = BBE_HIP(hipMemcpy(p->d_reqs, table.data(), table.size(), hipMemcpyHostToDevice))) !=
-        hipSuccess) {
+    if ((e = BBE_HIP(hipMemcpy(p->d_reqs, p->host_reqs.data(), req_bytes,
+                               hipMemcpyHostToDevice))) != hipSuccess ||
+        (e = hipMemcpy(d_states(p), p->host_states.data(), p->states_used,
+                       hipMemcpyHostToDevice)) != hipSuccess) {
         destroy(p);
         return hip_fail(e, "copying the request table");
     }
@@ -545,8 +574,9 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
     hipStream_t s = static_cast<hipStream_t>(stream);
 
     // Launch shape: tuned on this batch, or from the cache, or the default.
-    Shape best{4, 64, 1};
-    std::pair<int, int> key{p->device, size_class(generation_count(p->host_reqs))};
+    Shape best{1, 64, 1};
+    const uint64_t work = shared_generation_count(p->host_reqs, p->together);
+    std::pair<int, int> key{p->device, size_class(work)};
     bool have = false;
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -558,9 +588,15 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
         }
     }
     if ((flags & BBE_PLAN_AUTOTUNE) && !have) {
-        const Shape cands[] = {{4, 64, 1},  {2, 64, 1},  {1, 64, 1}, {4, 128, 1},
-                               {2, 128, 1}, {1, 128, 1}, {4, 256, 1}, {4, 64, 2},
-                               {1, 64, 2}};
+        // One wave per workgroup and one generation per item are at least as
+        // good as anything else (4096 waves are resident; us, items of 64 and
+        // of 128 simulations, then half the workgroups: 5806 items 1280, 1710,
+        // 1750; 8192 items 8110, 10820, 9480; 140000 items 16300, 16380, 25100;
+        // 4 waves per workgroup within 2%), except that with several items
+        // for each resident wave longer ones can end more evenly (22400 items
+        // 15.5, 14.5 ms): only there is there something to try.
+        std::vector<Shape> cands = {{1, 64, 1}};
+        if (work >= 4096u * 4u) cands.push_back({1, 128, 1});
         // Candidates are timed on the batch itself, or -- for a batch of
         // more than kTuneGens generations -- on the same requests with their
         // simulation counts scaled down to about that much work.
@@ -574,6 +610,7 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
         hipEvent_t ev0, ev1;
         (void)hipEventCreate(&ev0);
         (void)hipEventCreate(&ev1);
+        if (cands.size() < 2) cands.clear();  // nothing to compare
         for (const Shape& c : cands) {
             int rc = upload_work(p, c, tune, state_of, states.all);
             if (rc != BBE_OK) {
@@ -582,19 +619,19 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
                 destroy(p);
                 return rc;
             }
-            float ms_sum = 0.0f;
+            float ms_min = 1e30f;
             bool okc = true;
-            for (int rep = 0; rep < 3 && okc; ++rep) {
+            for (int rep = 0; rep < 4 && okc; ++rep) {
                 (void)hipEventRecord(ev0, s);
                 okc = enqueue(p, s) == hipSuccess;
                 (void)hipEventRecord(ev1, s);
                 (void)hipEventSynchronize(ev1);
                 float ms = 0.0f;
                 (void)hipEventElapsedTime(&ms, ev0, ev1);
-                if (rep > 0) ms_sum += ms;  // first run warms up
+                if (rep > 0) ms_min = std::min(ms_min, ms);  // first run warms up
             }
-            if (okc && ms_sum < best_ms) {
-                best_ms = ms_sum;
+            if (okc && ms_min < best_ms) {
+                best_ms = ms_min;
                 best = c;
             }
         }
@@ -655,9 +692,7 @@ BBE_API int bbe_batch_plan_set_states(bbe_batch_plan* plan, const bbe_state* sta
         // requests of one race that are given the same arrays (or, by the
         // table, the same values) share an entry
         if (r > 0 && plan->host_reqs[r - 1].rc.n == q.rc.n &&
-            plan->host_reqs[r - 1].rc.L == q.rc.L && states[r - 1].tick == states[r].tick &&
-            states[r - 1].pos == states[r].pos &&
-            states[r - 1].prev_step == states[r].prev_step) {
+            plan->host_reqs[r - 1].rc.L == q.rc.L && same_arrays(&states[r - 1], &states[r])) {
             state_of[r] = state_of[r - 1];
             continue;
         }
