@@ -773,7 +773,7 @@ int put_prefix(const bbe_request& q, uint32_t sim, float target, int idx, uint32
 }  // namespace
 
 // The host's part counts most (16384 requests with 5 to 20 competitors:
-// 1.95 ms, 0.40 of them GPU time, with whole 850-byte descriptors; 0.95 ms with
+// 1.95 ms, 0.40 of them GPU time, with whole 850-byte descriptors; 0.93 ms with
 // records of what the kernel reads, 260 bytes on average, and the races, which
 // lie apart from each other in memory, fetched ahead).
 BBE_API int bbe_prefix_batch(const bbe_request* reqs, const uint32_t* sims, const float* targets,

@@ -7,20 +7,21 @@
 // A team of lanes runs one simulation, lane c for competitor c, with no order
 // kept among them.  The Monte-Carlo kernels put a whole simulation in a lane
 // because they have enough of them; here a tick's latency is what counts, and
-// a team shortens it sixfold (the 20-competitor trace from the start, 270
-// ticks: 784 us in the lane-a-race form, 134 us so, 0.5 us a tick):
+// a team shortens it ninefold (the 20-competitor trace from the start, 270
+// ticks: 784 us in the lane-a-race form, 90 us so, 0.33 us a tick):
 //  - the competitor ahead is found by comparing with all n positions at once
-//    (each lane reads them from LDS: the smallest larger one, then the step of
-//    the first competitor that holds it, and that only in ticks in which some
-//    lane is blocked);
+//    (each lane reads them from LDS: the smallest larger one, a subtraction
+//    and half a three-way minimum each, then the step of the first competitor
+//    that holds it, and that only in ticks in which some lane is blocked);
 //  - the draws of a tick are ceil(n/8) Philox blocks, so a team computes those
 //    of G / ceil(n/8) ticks at a time, a block a lane, into an LDS table.
 // One simulation has the whole wave (G = 64: its draws are made for 21 ticks
-// at once at 20 competitors); a batch has two simulations in each wave (G =
+// at once at 20 competitors, and each half of the wave compares with half of
+// the competitors: 134 us without the halves and the subtractions); a batch has two simulations in each wave (G =
 // 32), which keeps the waves short of each other's races: in the lane-a-race
 // form a wave of 64 requests with 5 to 20 competitors ran each competitor
 // count's code one after the other (16384 mixed requests from the start line:
-// 6.9 ms of GPU time, 0.40 ms so).
+// 6.9 ms of GPU time, 0.35 ms so).
 #include "bettors.hpp"
 #include "kernels.hpp"
 #include "race_sim.hpp"
@@ -28,11 +29,11 @@
 namespace bbe {
 
 // A lane's competitor; lanes past the last one hold a competitor that stands
-// at -1 for good: behind everybody, ahead of nobody.
+// at 0 for good: ahead of nobody, and never blocked.
 struct TeamLane {
     float elo = 0.0f, espan16 = 0.0f, alpha = 0.0f, beta = 0.0f, theta = -1.0f;
     float gamma = 0.0f, tau = 0.0f;
-    float d = -1.0f, s = 0.0f;
+    float d = 0.0f, s = 0.0f;
 };
 
 // LDS of a team: the draw table, 8 draws a lane, and (position, step) of the
@@ -74,7 +75,9 @@ __device__ __forceinline__ TeamLane team_lane(const RaceConst& rc, const RacePac
 // competitor did, and the next tick -- both hold for the team (they give the
 // same answer in all its lanes).  A competitor at NaN has left the race.  A
 // competitor that reaches the line keeps its position of before the tick.
-// J >= n (a multiple of 4): the competitors looked at.
+// J >= n (a multiple of 4): the competitors looked at.  A team that has the
+// whole wave (G = 64) is there twice, lanes 32 + c as lanes c, and each half
+// looks at half of the competitors.
 template <int G, int J, class Before, class After>
 __device__ __forceinline__ void team_run(TeamLane& me, uint32_t c, uint32_t n, uint32_t draws,
                                          uint32_t pairs, float L, uint32_t t, uint32_t sim,
@@ -84,7 +87,10 @@ __device__ __forceinline__ void team_run(TeamLane& me, uint32_t c, uint32_t n, u
     constexpr uint32_t kAhead = G / kBlocks;   // ticks whose draws are made at once
     const uint32_t nb = (n + 7u) / 8u;
     const uint32_t my_tick = c / nb, my_block = c - my_tick * nb;
-    const uint32_t place = draws + 4u * min(c, n - 1u);
+    constexpr int kHalves = G == 64 ? 2 : 1, kRows = J / 2 / kHalves;
+    const uint32_t me_at = kHalves == 2 ? c & 31u : c;
+    const uint32_t look = pairs + (kHalves == 2 ? (c >> 5) * (16u * kRows) : 0u);
+    const uint32_t place = draws + 4u * min(me_at, n - 1u);
     const uint64_t team = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1) << (__lane_id() & ~(G - 1));
     uint32_t i = kAhead;
     for (;;) {
@@ -102,29 +108,39 @@ __device__ __forceinline__ void team_run(TeamLane& me, uint32_t c, uint32_t n, u
         }
         if (c < (uint32_t)J) lds_st(pairs + 8u * c, f32x2{me.d, me.s});
         wave_fence();
-        f32x4 q[J / 2];
+        f32x4 q[kRows];
 #pragma unroll
-        for (int j = 0; j < J / 2; ++j) q[j] = lds_ld<f32x4>(pairs + 16u * j);
+        for (int j = 0; j < kRows; ++j) q[j] = lds_ld<f32x4>(look + 16u * j);
         const float u = lds_ld<float>(place + 32u * nb * i);
         wave_fence();
         float R = me.alpha + me.beta * me.d;
         R = R + me.gamma * fminf((float)t, me.tau);
         float f = me.elo + me.espan16 * u;
-        // the smallest position ahead (positions are >= 0: ordered like their bits)
-        uint32_t near = 0x7F800000u;
+        // the smallest position ahead, from the distances between the bits
+        // (positions are >= 0: ordered like their bits; nobody ahead, and
+        // oneself, wrap to 2^31 and more)
+        const uint32_t past = __float_as_uint(me.d) + 1u;
+        uint32_t near = ~0u;
 #pragma unroll
-        for (int j = 0; j < J / 2; ++j) {
-            near = min(near, q[j].x > me.d ? __float_as_uint(q[j].x) : 0x7F800000u);
-            near = min(near, q[j].z > me.d ? __float_as_uint(q[j].z) : 0x7F800000u);
+        for (int j = 0; j < kRows; ++j)
+            near = min(near, min(__float_as_uint(q[j].x) - past, __float_as_uint(q[j].z) - past));
+        if constexpr (kHalves == 2) {
+            const auto h = __builtin_amdgcn_permlane32_swap(near, near, false, false);
+            near = min(h[0], h[1]);
         }
-        const float nd = __uint_as_float(near);
-        const bool blocked = nd - me.d <= me.theta;
+        const float nd = __uint_as_float(near + past);
+        const bool blocked = (int)near >= 0 && nd - me.d <= me.theta;
         if (__builtin_amdgcn_ballot_w64(blocked)) {
-            float ns = 0.0f;  // step of the lowest index among equal positions
+            float ns = -1.0f;  // step of the lowest index among equal positions
 #pragma unroll
-            for (int j = J / 2 - 1; j >= 0; --j) {
+            for (int j = kRows - 1; j >= 0; --j) {
                 ns = q[j].z == nd ? q[j].w : ns;
                 ns = q[j].x == nd ? q[j].y : ns;
+            }
+            if constexpr (kHalves == 2) {
+                const uint32_t v = __float_as_uint(ns);
+                const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+                ns = __uint_as_float((int)h[0] >= 0 ? h[0] : h[1]);
             }
             const float s_min =
                 __uint_as_float(min(__float_as_uint(me.s), __float_as_uint(ns)));
@@ -170,7 +186,7 @@ __global__ void __launch_bounds__(64) race_prefix_kernel(const PrefixArgs a) {
     __shared__ __attribute__((aligned(16))) char smem[kTeamBytes<64>];
     const uint32_t c = threadIdx.x, n = (uint32_t)a.rc.n;
     const uint32_t draws = lds_addr(smem), pairs = draws + 64 * 32;
-    TeamLane me = team_lane(a.rc, a.pace, a.d0, a.s0, a.id0, c, pairs);
+    TeamLane me = team_lane(a.rc, a.pace, a.d0, a.s0, a.id0, c & 31u, pairs);
     uint32_t t_end = a.t0;
     bool ok = true;
     team_run_any<64>(
@@ -201,7 +217,7 @@ __global__ void __launch_bounds__(64) race_trace_kernel(const TraceArgs a) {
     __shared__ __attribute__((aligned(16))) char smem[kTeamBytes<64>];
     const uint32_t c = threadIdx.x, n = (uint32_t)a.rc.n;
     const uint32_t draws = lds_addr(smem), pairs = draws + 64 * 32;
-    TeamLane me = team_lane(a.rc, a.pace, a.d0, a.s0, a.id0, c, pairs);
+    TeamLane me = team_lane(a.rc, a.pace, a.d0, a.s0, a.id0, c & 31u, pairs);
     if (c < n) a.trace[c] = me.d;
     uint32_t rows = 1;
     // at most max_rows - 1 <= 2^20 ticks
@@ -365,13 +381,15 @@ hipError_t launch_race_prefix(const PrefixArgs& a, hipStream_t s) {
 // fraction of that, but of every wave they fill, so the line lies where their
 // waves begin to queue: at so many simulations per competitor for teams of 8,
 // 16 and 32 lanes.  Measured on both sides, full orders, us (team / lane):
-//   n = 5   1000: 119 / 235    32768: 176 / 238     49152: 233 / 241
-//   n = 13  1000: 179 / 600    32768: 494 / 612     49152: 705 / 612
-//   n = 20  1000: 201 / 940    24576: 821 / 947     32768: 1064 / 947
+//   n = 5   1000: 111 / 235    30720: 167 / 236     40960: 188 / 236
+//   n = 8  49152: 222 / 338    65536: 277 / 338
+//   n = 13  8192: 176 / 600    31200: 452 / 605     41600: 559 / 605
+//   n = 17 19125: 607 / 935    25500: 736 / 935
+//   n = 20  8192: 305 / 940    22500: 686 / 940     30000: 861 / 940
 // One competitor needs no look at the others: a lane each, 80 against 105.
 bool team_mc_fits(int n, uint32_t n_sims) {
     if (n < 2) return false;
-    const uint32_t per = n <= 8 ? 7168u : n <= 16 ? 2560u : 1280u;
+    const uint32_t per = n <= 8 ? 8192u : n <= 16 ? 3200u : 1500u;
     return n_sims <= per * (uint32_t)n;
 }
 
@@ -393,9 +411,9 @@ hipError_t launch_race_trace(const TraceArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_prefix_batch(const uint32_t* records, const uint64_t* at, int n_reqs, uint32_t k0, uint32_t k1,
-                               uint32_t* tick_out, float* pos_out, float* prev_out,
-                               hipStream_t s) {
+hipError_t launch_prefix_batch(const uint32_t* records, const uint64_t* at, int n_reqs,
+                               uint32_t k0, uint32_t k1, uint32_t* tick_out, float* pos_out,
+                               float* prev_out, hipStream_t s) {
     if (n_reqs <= 0) return hipSuccess;
     hipLaunchKernelGGL(prefix_batch_kernel, dim3((unsigned)(((long)n_reqs + 1) / 2)), dim3(64), 0,
                        s, records, at, n_reqs, k0, k1, tick_out, pos_out, prev_out);

@@ -21,7 +21,7 @@ def torch():
 
 def _line(n):
     """The most simulations of n >= 2 competitors that get a team each."""
-    return n * (7168 if n <= 8 else 2560 if n <= 16 else 1280)
+    return n * (8192 if n <= 8 else 3200 if n <= 16 else 1500)
 
 
 @pytest.mark.parametrize("n", range(2, 21))
