@@ -123,7 +123,7 @@ Work build_work(const std::vector<bbe::ReqDesc>& reqs, const std::vector<uint32_
     struct Share {
         uint64_t rests = 0, over = 0;  // requests with a rest, simulations of the rests
         uint32_t open = UINT32_MAX;    // the group's item that is not full yet
-        double ticks = 0.0;
+        double ticks = -1.0;           // expected
     };
     std::vector<Share> shares(reqs.size());  // at a group's number
     for (size_t r = 0; r < reqs.size(); ++r) {
@@ -142,7 +142,7 @@ Work build_work(const std::vector<bbe::ReqDesc>& reqs, const std::vector<uint32_
     for (size_t r = 0; r < reqs.size(); ++r) {
         const bbe::ReqDesc& rq = reqs[r];
         Share& sh = shares[together[r]];
-        sh.ticks = expected_ticks(rq, states[state_of[r]]);
+        if (sh.ticks < 0.0) sh.ticks = expected_ticks(rq, states[state_of[r]]);
         const bool shared = (sh.over + 63) / 64 < sh.rests;
         const uint64_t own = shared ? rq.n_sims - rq.n_sims % 64 : rq.n_sims;
         const uint32_t n = (uint32_t)rq.rc.n;
@@ -474,10 +474,14 @@ void fill_desc(const bbe_request& q, bbe::ReqDesc& d) {
     d.stop_after = q.stop_after == 0 ? q.race->n : q.stop_after;
 }
 
-// Whether two states are given by the same arrays.
-bool same_arrays(const bbe_state* a, const bbe_state* b) {
+// Whether state b of n competitors equals state a, which has been validated.
+bool same_state(const bbe_state* a, const bbe_state* b, int n) {
     if (!a || !b) return a == b;
-    return a->tick == b->tick && a->pos == b->pos && a->prev_step == b->prev_step;
+    if (a->tick != b->tick || !b->pos || !b->prev_step) return false;
+    const size_t bytes = n * sizeof(float);
+    return (a->pos == b->pos || std::memcmp(a->pos, b->pos, bytes) == 0) &&
+           (a->prev_step == b->prev_step ||
+            std::memcmp(a->prev_step, b->prev_step, bytes) == 0);
 }
 
 }  // namespace
@@ -502,7 +506,7 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
         // a row of requests of one race from one state is looked at once
         const bool again = i > 0 && q.race == reqs[i - 1].race;
         int rc = BBE_OK;
-        if (again && same_arrays(q.state, reqs[i - 1].state)) {
+        if (again && same_state(reqs[i - 1].state, q.state, q.race->n)) {
             state_of[i] = state_of[i - 1];
         } else {
             bbe::StartState st;
@@ -689,10 +693,9 @@ BBE_API int bbe_batch_plan_set_states(bbe_batch_plan* plan, const bbe_state* sta
     Distinct<bbe::StartState> all((size_t)n_reqs);
     for (int r = 0; r < n_reqs; ++r) {
         const bbe::ReqDesc& q = plan->host_reqs[r];
-        // requests of one race that are given the same arrays (or, by the
-        // table, the same values) share an entry
+        // requests of one race in the same state share an entry
         if (r > 0 && plan->host_reqs[r - 1].rc.n == q.rc.n &&
-            plan->host_reqs[r - 1].rc.L == q.rc.L && same_arrays(&states[r - 1], &states[r])) {
+            plan->host_reqs[r - 1].rc.L == q.rc.L && same_state(&states[r - 1], &states[r], q.rc.n)) {
             state_of[r] = state_of[r - 1];
             continue;
         }
