@@ -400,7 +400,7 @@ def cfg0_leg(reps: int = 20):
                           "cov": float(np.std(ms) / np.mean(ms))},
             "sims_per_s": c["n_sims"] / med, "competitor_steps": csteps,
             "competitor_steps_per_s": csteps / med,
-            "note": "one generation of 64 simulations per wave: 16 waves on a 1024-wave chip, "
+            "note": "a team of 8 lanes per simulation: 125 waves on a chip of 1024 SIMDs, "
                     "so the launch is latency-bound"}
 
 

@@ -241,9 +241,9 @@ typedef struct bbe_request {
 
 typedef struct bbe_batch_plan bbe_batch_plan;
 
-/* Plan flag: time candidate launch shapes (waves per workgroup, simulations
- * per work item, workgroups per CU) on the batch itself and keep the
- * fastest; the choice is cached per device and batch size class for later
+/* Plan flag: where several launch shapes (waves per workgroup, simulations
+ * per work item, workgroups per CU) may be the best for the batch's size, time
+ * them on the batch itself and keep the fastest; the choice is cached per device and batch size class for later
  * plans, in memory and in a JSON file ($BBE_TUNE_CACHE if set, an empty
  * value for none; else $XDG_CACHE_HOME/bbe/tune.json or
  * $HOME/.cache/bbe/tune.json) keyed by the device (architecture, name, CU
@@ -253,13 +253,14 @@ typedef struct bbe_batch_plan bbe_batch_plan;
 
 /* Builds a plan for n_reqs (>= 1) requests (the many dry-run requests of
  * in-play bettors, paper Section 3 and Section 6): copies the request
- * descriptors and a work list (requests split into work items of whole
- * generations of 64 simulations, ordered by expected competitor-steps,
- * largest first) to the device, optionally autotunes, and captures into a
- * HIP graph the whole launch sequence: clear the outputs, reset the work
- * queue, run one persistent kernel over every item (each item with the
- * kernel's instance for its competitor count; races with a time term of R
- * in a second launch of the paced variant), compute probabilities.
+ * descriptors, their start states and a work list (requests split into work
+ * items of whole generations of 64 simulations, the remainders of requests
+ * that differ only in their simulations together, ordered by expected
+ * competitor-steps, largest first) to the device, optionally autotunes, and
+ * captures into a HIP graph the whole launch sequence: clear the outputs,
+ * reset the work queue, run one persistent kernel over every item (each item
+ * with the kernel's instance for its competitor count; races with a time term
+ * of R in a second launch of the paced variant), compute probabilities.
  *   win_counts  device uint64[n_reqs][BBE_MAX_COMPETITORS]: row r receives
  *               request r's win counts (columns >= its n stay 0).
  *   probs       device double[n_reqs][BBE_MAX_COMPETITORS] or NULL: row r
@@ -285,9 +286,11 @@ int bbe_batch_plan_launch(bbe_batch_plan *plan, void *stream);
  * every time it advances, paper Sections 3 and 6), keeping the plan's
  * graph.  `states` is a host array of the plan's n_reqs states, validated as
  * in bbe_race_sim (all of them first: on error the plan is unchanged).  The
- * request table is copied on `stream`, after the launches already enqueued
+ * states are copied on `stream`, after the launches already enqueued
  * there; launch the plan on the same stream.  The work order keeps the
- * expected lengths of the plan's creation.
+ * expected lengths of the plan's creation, and requests that share work
+ * items keep sharing them, whatever their states (fastest while those that
+ * had one state at the creation are given one again).
  * Errors: BBE_EINVAL, BBE_EDEVICE.                                          */
 int bbe_batch_plan_set_states(bbe_batch_plan *plan, const bbe_state *states, void *stream);
 
@@ -314,7 +317,7 @@ int bbe_prefix_batch(const bbe_request *reqs, const uint32_t *sims, const float 
 /* bbe_prefix_batch for callers that cannot allocate memory (code that must
  * not call hipMalloc, such as tight serving loops or harnesses that forbid
  * it): same arguments, same outputs, same errors, but no device or host
- * allocation.  The request descriptors are staged in a fixed device array
+ * allocation.  The requests' records are staged in a fixed device array
  * of BBE_PREFIX_NOALLOC_MAX entries (about 3 MB), one per GPU, held until
  * the process ends; n > BBE_PREFIX_NOALLOC_MAX is rejected with BBE_EINVAL.
  * Every call on a GPU shares that GPU's array: calls that overlap on one GPU
@@ -483,9 +486,8 @@ int bbe_mlp_forward_hidden(const bbe_mlp *m, const uint16_t *x, const int32_t *n
  * into loss (device float[1], overwritten), and its gradient into grad
  * (device float[BBE_MLP_NPARAMS], overwritten; NULL = the network's own
  * gradient buffer, used by bbe_mlp_adam_step with grad = NULL).  The
- * gradient is summed over the rows in a fixed order: the same inputs give
- * the same bits on every call (the loss is summed with atomics and may
- * differ in its last bits).                                                */
+ * gradient and the loss are summed over the rows in a fixed order: the same
+ * inputs give the same bits on every call.                                 */
 int bbe_mlp_loss_grad(bbe_mlp *m, const uint16_t *x, const int32_t *n_valid,
                       const float *target, int batch, float *loss, float *grad, void *stream);
 

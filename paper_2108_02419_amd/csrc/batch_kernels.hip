@@ -7,9 +7,10 @@
 // resident capacity of the GPU; every wave repeatedly takes the next work
 // item from a global atomic counter (one atomic per item, issued by lane
 // 0), runs that item's simulations one generation of 64 at a time with the
-// template instance of its competitor count and the request's parameters in
+// template instance of its competitor count and the race's parameters in
 // its LDS records, and flushes the item's wins with one 64-bit atomic per
-// competitor.  Items are ordered by expected work, largest first, so the
+// competitor (items shared by requests: one per simulation, to its request's
+// row).  Items are ordered by expected work, largest first, so the
 // smallest work ends the queue.
 #include "batch_mc.hpp"
 #include "kernels.hpp"

@@ -4,10 +4,11 @@
 //
 // bettor_views_kernel: a workgroup forms the views of some slices of 1024
 // bettors, each grouped by kind so that nearly every wave runs a single rule,
-// at chunks of kViewRowsPerBlock trace rows.  Per chunk it stages the rows in LDS -- with up
-// to kViewWindow rows of history before them where there are LinEx bettors --
-// and settles everything that does not depend on the bettor once: each row's
-// leader and runner-up, and LinEx's pick for every window up to the longest.
+// at chunks of kViewRowsPerBlock trace rows.  Per chunk it stages the rows in
+// LDS -- with up to kViewWindow rows of history before them where there are
+// LinEx bettors -- and settles everything that does not depend on the bettor
+// once: each row's leader and runner-up, and LinEx's pick for every window up
+// to the longest.
 // A bettor's view is then a look-up:
 //   LW     the leader (ties to the lowest index);
 //   UD     the runner-up while fl(x_P1 - x_P2) < D, else the leader;
@@ -21,10 +22,10 @@
 //          of the Philox block with counter (t, bettor, ~0, ~0).
 // The views go to memory through LDS, in the caller's order and 16 bytes at a
 // time; ZI's and LinEx's tallies have 16 copies of each bin in LDS, since most
-// bettors back the same few competitors, and the others' are counted by wave.  (With a scan per LinEx bettor, byte stores and
-// one copy of the bins, 10^5 bettors took 140 us for 240 rows of a
-// 20-competitor race, 46 us so; what is left is ZI's Philox rounds and the
-// 24 MB of views.)
+// bettors back the same few competitors, and the others' are counted by wave.
+// (With a scan per LinEx bettor, byte stores and one copy of the bins, 10^5
+// bettors took 140 us for 240 rows of a 20-competitor race, 46 us so; what is
+// left is ZI's Philox rounds and the 24 MB of views.)
 #include "bettors.hpp"
 #include "race_sim.hpp"
 
