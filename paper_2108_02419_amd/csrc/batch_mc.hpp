@@ -41,7 +41,8 @@ constexpr int batch_skip_step() {
 // One work item.  The simulations of an item with kChunkLanes may belong to
 // several requests, all of the same race and stop_after.  They start from the
 // same state unless the states were changed since the items were made: a
-// generation then runs once for each state among its lanes.
+// generation then runs once for each state among its lanes (where there are
+// more than a few, the host launches items without shared lanes instead).
 // What differs by lane is read from LDS where it is used, by the items of one
 // request too: a variant with scalar indices for those was 2% faster at 5
 // competitors and equal or up to 2% slower from 9 on (40000 requests of 100 or

@@ -67,15 +67,17 @@ class Distinct {
 
   private:
     static uint64_t hash(const T& v) {
-        static_assert(sizeof(T) % 4 == 0);
-        uint32_t w;
-        uint64_t h = 0;
-        for (size_t i = 0; i < sizeof(T); i += 4) {
-            std::memcpy(&w, reinterpret_cast<const char*>(&v) + i, 4);
-            h = (h ^ w) * 0x9E3779B97F4A7C15ull;
-            h ^= h >> 32;
+        static_assert(sizeof(T) % 8 == 0);
+        // four chains of products at a time, as each waits on its last
+        uint64_t h[4] = {1, 2, 3, 4};
+        for (size_t i = 0; i < sizeof(T); i += 8) {
+            uint64_t w;
+            std::memcpy(&w, reinterpret_cast<const char*>(&v) + i, 8);
+            uint64_t& x = h[i / 8 % 4];
+            x = (x ^ w) * 0x9E3779B97F4A7C15ull;
+            x ^= x >> 32;
         }
-        return h;
+        return h[0] ^ (h[1] >> 7) ^ (h[2] >> 13) ^ (h[3] >> 19);
     }
     std::vector<uint32_t> slots_;
     uint32_t last_ = 0;
@@ -118,7 +120,7 @@ double expected_ticks(const bbe::ReqDesc& r, const bbe::StartState& st) {
 // their states and launching them took 2.54 ms before and 1.20 ms so.
 Work build_work(const std::vector<bbe::ReqDesc>& reqs, const std::vector<uint32_t>& state_of,
                 const std::vector<bbe::StartState>& states,
-                const std::vector<uint32_t>& together, int sims_per_item) {
+                const std::vector<uint32_t>& together, int sims_per_item, bool share) {
     Work w;
     struct Share {
         uint64_t rests = 0, over = 0;  // requests with a rest, simulations of the rests
@@ -143,7 +145,7 @@ Work build_work(const std::vector<bbe::ReqDesc>& reqs, const std::vector<uint32_
         const bbe::ReqDesc& rq = reqs[r];
         Share& sh = shares[together[r]];
         if (sh.ticks < 0.0) sh.ticks = expected_ticks(rq, states[state_of[r]]);
-        const bool shared = (sh.over + 63) / 64 < sh.rests;
+        const bool shared = share && (sh.over + 63) / 64 < sh.rests;
         const uint64_t own = shared ? rq.n_sims - rq.n_sims % 64 : rq.n_sims;
         const uint32_t n = (uint32_t)rq.rc.n;
         for (uint64_t first = 0; first < own; first += (uint64_t)sims_per_item) {
@@ -308,16 +310,27 @@ int size_class(size_t n_chunks) {
 
 }  // namespace
 
+// A work list on the device and its captured launch sequence.
+struct Sequence {
+    char* d_work = nullptr;  // the work items, then their lane table
+    size_t work_cap = 0;     // bytes
+    uint32_t n_chunks = 0;
+    std::vector<Group> groups;
+    std::vector<int> grids;
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
+};
+
 struct bbe_batch_plan {
     int device = 0;
     int n_reqs = 0;
     bbe::ReqDesc* d_reqs = nullptr;  // the requests, then their states (host_states)
-    char* d_work = nullptr;          // the work items, then their lane table
-    size_t work_cap = 0;             // bytes
     uint32_t* d_queue = nullptr;  // one work-queue head per group
-    uint32_t n_chunks = 0;
-    std::vector<Group> groups;
-    std::vector<int> grids;
+    // requests share waves in `shared` and do not in `alone`, which is made
+    // when the states first call for it (see state_runs)
+    Sequence shared, alone;
+    bool apart = false;  // launch `alone`
+    uint64_t shared_gens = 0, alone_gens = 0;
     uint32_t k0 = 0, k1 = 0;
     unsigned long long* wins = nullptr;
     double* probs = nullptr;
@@ -325,8 +338,6 @@ struct bbe_batch_plan {
     Shape shape{1, 64, 1};
     int item_sims = 64;  // simulations per work item in use (>= shape.sims_per_item)
     hipStream_t cap_stream = nullptr;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
     std::vector<bbe::ReqDesc> host_reqs;
     std::vector<uint32_t> together;
     std::vector<char> host_states;  // each request's state's number, then the states
@@ -351,28 +362,28 @@ void keep_states(bbe_batch_plan* p, const std::vector<uint32_t>& state_of,
     p->states_used = at + states.size() * sizeof(bbe::StartState);
 }
 
-hipError_t enqueue(bbe_batch_plan* p, hipStream_t s) {
+hipError_t enqueue(bbe_batch_plan* p, const Sequence& q, hipStream_t s) {
     hipError_t e;
     if ((e = bbe::launch_zero_u64(p->wins, p->n_reqs * bbe::kMaxN, s)) != hipSuccess) return e;
     if (p->steps && (e = bbe::launch_zero_u64(p->steps, 1, s)) != hipSuccess) return e;
-    if ((e = bbe::launch_fill_u32(p->d_queue, 0u, (int)p->groups.size(), s)) != hipSuccess)
+    if ((e = bbe::launch_fill_u32(p->d_queue, 0u, (int)q.groups.size(), s)) != hipSuccess)
         return e;
-    for (size_t g = 0; g < p->groups.size(); ++g) {
-        const Group& gr = p->groups[g];
+    for (size_t g = 0; g < q.groups.size(); ++g) {
+        const Group& gr = q.groups[g];
         bbe::BatchArgs a;
         a.reqs = p->d_reqs;
-        a.chunks = reinterpret_cast<const bbe::Chunk*>(p->d_work) + gr.first;
+        a.chunks = reinterpret_cast<const bbe::Chunk*>(q.d_work) + gr.first;
         a.n_chunks = gr.count;
         a.state_of = reinterpret_cast<const uint32_t*>(d_states(p));
         a.states = reinterpret_cast<const bbe::StartState*>(d_states(p) + states_at(p->n_reqs));
-        a.lanes = reinterpret_cast<const bbe::PackLane*>(p->d_work +
-                                                         p->n_chunks * sizeof(bbe::Chunk));
+        a.lanes = reinterpret_cast<const bbe::PackLane*>(q.d_work +
+                                                         q.n_chunks * sizeof(bbe::Chunk));
         a.queue = p->d_queue + g;
         a.wins = p->wins;
         a.steps = p->steps;
         a.k0 = p->k0;
         a.k1 = p->k1;
-        if ((e = bbe::launch_batch_mc(a, p->shape.waves_per_block, p->grids[g], gr.paced, s)) !=
+        if ((e = bbe::launch_batch_mc(a, p->shape.waves_per_block, q.grids[g], gr.paced, s)) !=
             hipSuccess)
             return e;
     }
@@ -413,30 +424,31 @@ int item_sims(const std::vector<bbe::ReqDesc>& reqs, int sims_per_item) {
     return (int)std::max<uint64_t>((uint64_t)sims_per_item, 64u * min_gens);
 }
 
-int upload_work(bbe_batch_plan* p, const Shape& sh, const std::vector<bbe::ReqDesc>& reqs,
-                const std::vector<uint32_t>& state_of,
+// Puts a work list on the device.
+int upload_work(bbe_batch_plan* p, Sequence& q, const Shape& sh,
+                const std::vector<bbe::ReqDesc>& reqs, const std::vector<uint32_t>& state_of,
                 const std::vector<bbe::StartState>& states) {
     const int per_item = item_sims(reqs, sh.sims_per_item);
-    Work w = build_work(reqs, state_of, states, p->together, per_item);
+    Work w = build_work(reqs, state_of, states, p->together, per_item, &q == &p->shared);
     const size_t items = w.chunks.size() * sizeof(bbe::Chunk);
     std::vector<char> h(items + w.lanes.size() * sizeof(bbe::PackLane));
     std::memcpy(h.data(), w.chunks.data(), items);
     if (!w.lanes.empty()) std::memcpy(h.data() + items, w.lanes.data(), h.size() - items);
-    if (h.size() > p->work_cap) {
-        if (p->d_work) (void)hipFree(p->d_work);
-        p->d_work = nullptr;
-        p->work_cap = 0;
-        if (dev_alloc(&p->d_work, h.size()) != hipSuccess)
+    if (h.size() > q.work_cap) {
+        if (q.d_work) (void)hipFree(q.d_work);
+        q.d_work = nullptr;
+        q.work_cap = 0;
+        if (dev_alloc(&q.d_work, h.size()) != hipSuccess)
             return fail(BBE_ENOMEM, "device allocation of the work list failed");
-        p->work_cap = h.size();
+        q.work_cap = h.size();
     }
-    hipError_t e = BBE_HIP(hipMemcpy(p->d_work, h.data(), h.size(), hipMemcpyHostToDevice));
+    hipError_t e = BBE_HIP(hipMemcpy(q.d_work, h.data(), h.size(), hipMemcpyHostToDevice));
     if (e != hipSuccess) return hip_fail(e, "copying the work list");
-    p->n_chunks = (uint32_t)w.chunks.size();
+    q.n_chunks = (uint32_t)w.chunks.size();
+    q.groups = w.groups;
+    q.grids.clear();
     p->shape = sh;
     p->item_sims = per_item;
-    p->groups = w.groups;
-    p->grids.clear();
     const int cus = device_cus();
     for (const Group& g : w.groups) {
         // resident capacity (or a share of it), but no more waves than the
@@ -445,19 +457,76 @@ int upload_work(bbe_batch_plan* p, const Shape& sh, const std::vector<bbe::ReqDe
                                     sh.cu_share) *
                    cus;
         long need = ((long)g.count + sh.waves_per_block - 1) / sh.waves_per_block;
-        p->grids.push_back((int)std::max(1L, std::min(cap, need)));
+        q.grids.push_back((int)std::max(1L, std::min(cap, need)));
     }
     return BBE_OK;
 }
 
+// Captures clear -> queue reset -> persistent kernel -> probabilities.
+int capture(bbe_batch_plan* p, Sequence& q) {
+    hipError_t e;
+    if ((e = BBE_HIP(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal))) !=
+        hipSuccess)
+        return hip_fail(e, "beginning graph capture");
+    hipError_t ee = enqueue(p, q, p->cap_stream);
+    e = hipStreamEndCapture(p->cap_stream, &q.graph);
+    if (ee != hipSuccess || e != hipSuccess)
+        return hip_fail(ee != hipSuccess ? ee : e, "capturing the launch sequence");
+    if ((e = BBE_HIP(hipGraphInstantiate(&q.exec, q.graph, nullptr, nullptr, 0))) != hipSuccess)
+        return hip_fail(e, "instantiating the graph");
+    return BBE_OK;
+}
+
+void release(Sequence& q) {
+    if (q.exec) (void)hipGraphExecDestroy(q.exec);
+    if (q.graph) (void)hipGraphDestroy(q.graph);
+    if (q.d_work) (void)hipFree(q.d_work);
+    q = Sequence();
+}
+
+// Makes `alone` on the plan's device, also while this thread captures another
+// stream.
+bool make_alone(bbe_batch_plan* p, const std::vector<uint32_t>& state_of,
+                const std::vector<bbe::StartState>& states) {
+    int dev = p->device;
+    (void)hipGetDevice(&dev);
+    if (dev != p->device && hipSetDevice(p->device) != hipSuccess) return false;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    const bool made =
+        upload_work(p, p->alone, p->shape, p->host_reqs, state_of, states) == BBE_OK &&
+        capture(p, p->alone) == BBE_OK;
+    if (!made) release(p->alone);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (dev != p->device) (void)hipSetDevice(dev);
+    return made;
+}
+
+// The most runs of equal states that the requests of a group are in.  A wave of
+// the shared list goes through its lanes' states one after the other, so
+// `alone` is launched once that may be more generations than it has itself: 10^4
+// requests of one simulation, all of different states, would be 157 waves with 64
+// states each.
+uint64_t state_runs(const std::vector<uint32_t>& together,
+                    const std::vector<uint32_t>& state_of) {
+    std::vector<uint32_t> last(together.size(), UINT32_MAX), runs(together.size());
+    uint32_t most = 1;
+    for (size_t r = 0; r < together.size(); ++r) {
+        const uint32_t g = together[r];
+        if (last[g] == state_of[r]) continue;
+        last[g] = state_of[r];
+        most = std::max(most, ++runs[g]);
+    }
+    return most;
+}
+
 void destroy(bbe_batch_plan* p) {
     if (!p) return;
-    if (p->d_reqs || p->d_work || p->d_queue || p->exec) (void)hipDeviceSynchronize();
-    if (p->exec) (void)hipGraphExecDestroy(p->exec);
-    if (p->graph) (void)hipGraphDestroy(p->graph);
+    if (p->d_reqs || p->d_queue) (void)hipDeviceSynchronize();
+    release(p->shared);
+    release(p->alone);
     if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
     if (p->d_reqs) (void)hipFree(p->d_reqs);
-    if (p->d_work) (void)hipFree(p->d_work);
     if (p->d_queue) (void)hipFree(p->d_queue);
     delete p;
 }
@@ -579,7 +648,9 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
 
     // Launch shape: tuned on this batch, or from the cache, or the default.
     Shape best{1, 64, 1};
-    const uint64_t work = shared_generation_count(p->host_reqs, p->together);
+    p->alone_gens = generation_count(p->host_reqs);
+    p->shared_gens = shared_generation_count(p->host_reqs, p->together);
+    const uint64_t work = p->shared_gens;
     std::pair<int, int> key{p->device, size_class(work)};
     bool have = false;
     {
@@ -616,7 +687,7 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
         (void)hipEventCreate(&ev1);
         if (cands.size() < 2) cands.clear();  // nothing to compare
         for (const Shape& c : cands) {
-            int rc = upload_work(p, c, tune, state_of, states.all);
+            int rc = upload_work(p, p->shared, c, tune, state_of, states.all);
             if (rc != BBE_OK) {
                 (void)hipEventDestroy(ev0);
                 (void)hipEventDestroy(ev1);
@@ -627,7 +698,7 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
             bool okc = true;
             for (int rep = 0; rep < 4 && okc; ++rep) {
                 (void)hipEventRecord(ev0, s);
-                okc = enqueue(p, s) == hipSuccess;
+                okc = enqueue(p, p->shared, s) == hipSuccess;
                 (void)hipEventRecord(ev1, s);
                 (void)hipEventSynchronize(ev1);
                 float ms = 0.0f;
@@ -645,29 +716,13 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
         g_tuned[key] = best;
         store_tune_entry(p->device, key.second, best);
     }
-    int rc = upload_work(p, best, p->host_reqs, state_of, states.all);
+    int rc = upload_work(p, p->shared, best, p->host_reqs, state_of, states.all);
+    if (rc == BBE_OK) rc = capture(p, p->shared);
     if (rc != BBE_OK) {
         destroy(p);
         return rc;
     }
 
-    // Capture clear -> queue reset -> persistent kernel -> probabilities.
-    if ((e = BBE_HIP(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal))) !=
-        hipSuccess) {
-        destroy(p);
-        return hip_fail(e, "beginning graph capture");
-    }
-    hipError_t ee = enqueue(p, p->cap_stream);
-    e = hipStreamEndCapture(p->cap_stream, &p->graph);
-    if (ee != hipSuccess || e != hipSuccess) {
-        destroy(p);
-        return hip_fail(ee != hipSuccess ? ee : e, "capturing the launch sequence");
-    }
-    if ((e = BBE_HIP(hipGraphInstantiate(&p->exec, p->graph, nullptr, nullptr, 0))) !=
-        hipSuccess) {
-        destroy(p);
-        return hip_fail(e, "instantiating the graph");
-    }
     if ((e = hipStreamSynchronize(s)) != hipSuccess) {
         destroy(p);
         return hip_fail(e, "synchronizing after plan set-up");
@@ -677,41 +732,49 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
 }
 
 BBE_API int bbe_batch_plan_launch(bbe_batch_plan* plan, void* stream) {
-    if (!plan || !plan->exec) return fail(BBE_EINVAL, "plan is NULL");
-    hipError_t e = BBE_HIP(hipGraphLaunch(plan->exec, static_cast<hipStream_t>(stream)));
+    if (!plan || !plan->shared.exec) return fail(BBE_EINVAL, "plan is NULL");
+    const Sequence& q = plan->apart ? plan->alone : plan->shared;
+    hipError_t e = BBE_HIP(hipGraphLaunch(q.exec, static_cast<hipStream_t>(stream)));
     if (e != hipSuccess) return hip_fail(e, "launching the plan graph");
     return ok();
 }
 
 BBE_API int bbe_batch_plan_set_states(bbe_batch_plan* plan, const bbe_state* states,
                                       void* stream) {
-    if (!plan || !plan->exec) return fail(BBE_EINVAL, "plan is NULL");
+    if (!plan || !plan->shared.exec) return fail(BBE_EINVAL, "plan is NULL");
     if (!states) return fail(BBE_EINVAL, "states is NULL");
     const int n_reqs = plan->n_reqs;
-    // validate every state before touching the plan
-    std::vector<uint32_t> state_of(n_reqs);
-    Distinct<bbe::StartState> all((size_t)n_reqs);
+    // validate every state before touching the plan; a request in the state of
+    // the one before it in its group shares that one's entry
+    std::vector<uint32_t> state_of(n_reqs), before(n_reqs, UINT32_MAX);
+    std::vector<bbe::StartState> distinct;
+    distinct.reserve(n_reqs);
     for (int r = 0; r < n_reqs; ++r) {
         const bbe::ReqDesc& q = plan->host_reqs[r];
-        // requests of one race in the same state share an entry
-        if (r > 0 && plan->host_reqs[r - 1].rc.n == q.rc.n &&
-            plan->host_reqs[r - 1].rc.L == q.rc.L && same_state(&states[r - 1], &states[r], q.rc.n)) {
-            state_of[r] = state_of[r - 1];
-            continue;
+        uint32_t& b = before[plan->together[r]];
+        if (b != UINT32_MAX && same_state(&states[b], &states[r], q.rc.n)) {
+            state_of[r] = state_of[b];
+        } else {
+            state_of[r] = (uint32_t)distinct.size();
+            distinct.emplace_back();
+            bbe::StartState& st = distinct.back();
+            int rc = check_state(q.rc.n, q.rc.L, &states[r], st.d0, st.s0, st.id0, &st.t0);
+            if (rc != BBE_OK) return fail(rc, "request %d: %s", r, g_err.c_str());
         }
-        bbe::StartState st;
-        std::memset(&st, 0, sizeof st);
-        int rc = check_state(q.rc.n, q.rc.L, &states[r], st.d0, st.s0, st.id0, &st.t0);
-        if (rc != BBE_OK) return fail(rc, "request %d: %s", r, g_err.c_str());
-        state_of[r] = all.number(st);
+        b = (uint32_t)r;
     }
-    keep_states(plan, state_of, all.all);
-    // ordered after earlier launches on `stream`; the pageable source is
-    // consumed before the call returns.  A copy that a graph records takes the
-    // whole table, which may hold more states when the graph runs.
+    keep_states(plan, state_of, distinct);
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     (void)hipStreamIsCapturing(s, &cap);
+    plan->apart = plan->shared_gens < plan->alone_gens &&
+                  state_runs(plan->together, state_of) * plan->shared_gens > plan->alone_gens;
+    // `shared` gives the same results where `alone` cannot be made now
+    if (plan->apart && !plan->alone.exec)
+        plan->apart = cap == hipStreamCaptureStatusNone && make_alone(plan, state_of, distinct);
+    // ordered after earlier launches on `stream`; the pageable source is
+    // consumed before the call returns.  A copy that a graph records takes the
+    // whole table, which may hold more states when the graph runs.
     hipError_t e = BBE_HIP(hipMemcpyAsync(
         d_states(plan), plan->host_states.data(),
         cap == hipStreamCaptureStatusNone ? plan->states_used : plan->host_states.size(),
@@ -726,11 +789,11 @@ BBE_API int bbe_batch_plan_info(const bbe_batch_plan* plan, int* waves_per_block
     if (waves_per_block) *waves_per_block = plan->shape.waves_per_block;
     if (grid) {
         int g = 0;
-        for (int x : plan->grids) g = std::max(g, x);
+        for (int x : plan->shared.grids) g = std::max(g, x);
         *grid = g;
     }
     if (sims_per_item) *sims_per_item = plan->item_sims;
-    if (n_items) *n_items = (int)plan->n_chunks;
+    if (n_items) *n_items = (int)plan->shared.n_chunks;
     return ok();
 }
 

@@ -73,3 +73,31 @@ def test_requests_that_share_waves(torch, orc, n, paced):
             pos[i, :len(s[1])], prev[i, :len(s[2])] = s[1], s[2]
         plan.set_states(tick, pos, prev)
         check(plan, wins, steps, states, what)
+
+
+@pytest.mark.parametrize("split", [1, 20, 39])
+def test_two_states_in_a_shared_wave(torch, orc, split):
+    """Many small requests, the first `split` from one state and the others
+    from another: shared waves run once for each."""
+    rng = np.random.default_rng(split)
+    comp = inputs.competitor_params(rng, 9)
+    race = Race(comp, L)
+    specs = [(race, None, 0, 1 + i % 9, 70 + i, 0) for i in range(40)]
+    wins = torch.zeros((40, 20), dtype=torch.int64, device="cuda")
+    steps = torch.zeros(1, dtype=torch.int64, device="cuda")
+    plan = BatchPlan(specs, SEED, wins, None, steps, autotune=False)
+    a, b = _state(orc, comp, 500.0), _state(orc, comp, 1100.0)
+    states = [a if i < split else b for i in range(40)]
+    plan.set_states(np.array([s[0] for s in states], np.uint32),
+                    np.array([s[1] for s in states]), np.array([s[2] for s in states]))
+    announce(f"shared waves, {split} of 40 requests in another state")
+    for _ in range(2):
+        plan.launch()
+    torch.cuda.synchronize()
+    total = 0
+    for i, (_, _, _, n_sims, request, _) in enumerate(specs):
+        _, w, s = orc.race_sim(comp, L, n_sims, SEED, request=request, state=states[i],
+                               want_orders=False)
+        np.testing.assert_array_equal(wins[i, :9].cpu().numpy().astype(np.uint64), w)
+        total += s
+    assert int(steps.item()) == total
