@@ -288,9 +288,11 @@ int bbe_batch_plan_launch(bbe_batch_plan *plan, void *stream);
  * in bbe_race_sim (all of them first: on error the plan is unchanged).  The
  * states are copied on `stream`, after the launches already enqueued
  * there; launch the plan on the same stream.  The work order keeps the
- * expected lengths of the plan's creation, and requests that share work
- * items keep sharing them, whatever their states (fastest while those that
- * had one state at the creation are given one again).
+ * expected lengths of the plan's creation.  Requests that share work items
+ * because they had one state then are fastest while they are given one
+ * state again; given many, the plan goes over to items of one request each,
+ * which the first such call prepares (a device allocation; not in a stream
+ * that is being captured, where the shared items are kept).
  * Errors: BBE_EINVAL, BBE_EDEVICE.                                          */
 int bbe_batch_plan_set_states(bbe_batch_plan *plan, const bbe_state *states, void *stream);
 
