@@ -54,6 +54,18 @@ __device__ __forceinline__ int linex_scan(const float* __restrict__ x,
     return best;
 }
 
+// Leader and runner-up (the leader where n = 1) of a row that holds NaN, as a
+// scan finds them: a NaN is passed by nobody and passes nobody.
+__device__ __forceinline__ void scan_row(const float* x, int n, int& p1, int& p2) {
+    p1 = 0;
+    for (int c = 1; c < n; ++c)
+        if (x[c] > x[p1]) p1 = c;
+    p2 = -1;
+    for (int c = 0; c < n; ++c)
+        if (c != p1 && (p2 < 0 || x[c] > x[p2])) p2 = c;
+    if (p2 < 0) p2 = p1;
+}
+
 constexpr int kViewThreads = 256;
 constexpr int kViewEach = kViewSlice / kViewThreads;
 constexpr int kViewCopies = 16;
@@ -90,14 +102,30 @@ __global__ void __launch_bounds__(kViewThreads)
         for (int k = threadIdx.x; k < nr * n * kViewCopies; k += kViewThreads) s_cnt[k] = 0u;
         __syncthreads();
         // a thread for each row and competitor: the leader has nobody before
-        // it in (position, lowest index) order, the runner-up one
+        // it in (position, lowest index) order, the runner-up one; NaN has no
+        // place in that order, so a row with one is scanned
         for (int k = threadIdx.x; k < nr * n; k += kViewThreads) {
             const int ii = k / n, c = k - ii * n;
             const float* x = s_rows + ((int)(r0 - lo) + ii) * kStride;
             const float xc = x[c];
             int before = 0;
+            bool nan = false;
 #pragma unroll 4
-            for (int j = 0; j < n; ++j) before += x[j] > xc || (x[j] == xc && j < c);
+            for (int j = 0; j < n; ++j) {
+                before += x[j] > xc || (x[j] == xc && j < c);
+                nan |= x[j] != x[j];
+            }
+            if (nan) {
+                int p1, p2;
+                if (c == 0) {
+                    scan_row(x, n, p1, p2);
+                    s_p1[ii] = p1;
+                    s_x1[ii] = x[p1];
+                    s_p2[ii] = p2;
+                    s_x2[ii] = x[p2];
+                }
+                continue;
+            }
             if (before == 0) {
                 s_p1[ii] = c;
                 s_x1[ii] = xc;
