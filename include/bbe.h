@@ -290,14 +290,14 @@ int bbe_batch_plan_launch(bbe_batch_plan *plan, void *stream);
  * there; launch the plan on the same stream.  The work order keeps the
  * expected lengths of the plan's creation.  Requests that share work items
  * because they had one state then are fastest while they are given one
- * state again; given many, the plan goes over to items of one request each,
- * which the first such call prepares (a device allocation; not in a stream
- * that is being captured, where the shared items are kept).
+ * state again; given several, the plan goes over to items of one request each
+ * wherever the shared ones could take longer.
  * Errors: BBE_EINVAL, BBE_EDEVICE.                                          */
 int bbe_batch_plan_set_states(bbe_batch_plan *plan, const bbe_state *states, void *stream);
 
 /* Launch shape chosen for a plan (any output pointer may be NULL); `grid`
- * is the largest grid among the plan's per-competitor-count kernels. */
+ * is the largest grid among the plan's launches, `n_items` the work items of
+ * its requests from their present states. */
 int bbe_batch_plan_info(const bbe_batch_plan *plan, int *waves_per_block, int *grid,
                         int *sims_per_item, int *n_items);
 

@@ -41,8 +41,8 @@ constexpr int batch_skip_step() {
 // One work item.  The simulations of an item with kChunkLanes may belong to
 // several requests, all of the same race and stop_after.  They start from the
 // same state unless the states were changed since the items were made: a
-// generation then runs once for each state among its lanes (where there are
-// more than a few, the host launches items without shared lanes instead).
+// generation then runs once for each state among its lanes (where that takes
+// longer than items without shared lanes, the launch takes those).
 // What differs by lane is read from LDS where it is used, by the items of one
 // request too: a variant with scalar indices for those was 2% faster at 5
 // competitors and equal or up to 2% slower from 9 on (40000 requests of 100 or
@@ -142,12 +142,17 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
     const int lane = threadIdx.x & 63;
     const uint32_t wbase = wave * kWaveBytes;
     unsigned long long steps = 0ull;
+    // read where the launch runs, so that it fits the states there, also when
+    // a graph replays it
+    const bool apart = *a.apart != 0u;
+    const Chunk* const chunks = apart ? a.alone : a.chunks;
+    const uint32_t n_chunks = apart ? a.n_alone : a.n_chunks;
     for (;;) {
         uint32_t ci = 0;
         if (lane == 0) ci = atomicAdd(a.queue, 1u);
         ci = __builtin_amdgcn_readfirstlane(ci);
-        if (ci >= a.n_chunks) break;
-        const Chunk ch = a.chunks[ci];
+        if (ci >= n_chunks) break;
+        const Chunk ch = chunks[ci];
         const int n = (int)(__builtin_amdgcn_readfirstlane(ch.n) & ~kChunkLanes);
         run_chunk_any<kPaced>(n, a, ch, smem, wbase, lane, steps,
                               std::make_integer_sequence<int, kMaxN>{});

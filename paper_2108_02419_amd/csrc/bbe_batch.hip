@@ -35,11 +35,14 @@ struct Group {
     uint32_t first;  // its items: chunks[first .. first + count)
     uint32_t count;
     bool paced;      // the items of races with a time term of R
+    // the items of the same requests without shared waves (first and count
+    // again where nothing is shared)
+    uint32_t alone_first, alone_count;
 };
 
 struct Work {
-    std::vector<bbe::Chunk> chunks;
-    std::vector<bbe::PackLane> lanes;
+    std::unique_ptr<char[]> bytes;  // the items (of both lists), then the lane table
+    size_t size = 0, n_chunks = 0;
     std::vector<Group> groups;
 };
 
@@ -111,6 +114,36 @@ double expected_ticks(const bbe::ReqDesc& r, const bbe::StartState& st) {
     return first + f * (all - first);
 }
 
+// An item and its place in the order of a launch: plain items first (one
+// launch), then paced ones (another), each largest first.
+struct Item {
+    uint32_t order;
+    bbe::Chunk c;
+    static uint32_t place(bool paced, double work) {
+        const float w = (float)work;  // positive: ordered like its bits
+        uint32_t bits;
+        std::memcpy(&bits, &w, sizeof bits);
+        return (paced ? 0x80000000u : 0u) | (0x7FFFFFFFu - bits);
+    }
+};
+
+// Puts the items in their order at chunks[at ..]; returns their groups.
+std::vector<Group> put_items(std::vector<Item>& items, bbe::Chunk* chunks, size_t at) {
+    std::stable_sort(items.begin(), items.end(),
+                     [](const Item& a, const Item& b) { return a.order < b.order; });
+    std::vector<Group> groups;
+    for (const Item& it : items) {
+        const bool paced = it.order >> 31;
+        if (groups.empty() || groups.back().paced != paced)
+            groups.push_back({(uint32_t)at, 0u, paced, 0u, 0u});
+        groups.back().count += 1;
+        chunks[at++] = it.c;
+    }
+    return groups;
+}
+
+// The work list, and behind it the items of the list without shared waves.
+//
 // Requests that differ in nothing but their simulations (together[r], the
 // number of r's group, is the same) share waves: what is left of each after
 // whole generations of 64 goes to the lane table, request after request.
@@ -120,71 +153,68 @@ double expected_ticks(const bbe::ReqDesc& r, const bbe::StartState& st) {
 // their states and launching them took 2.54 ms before and 1.20 ms so.
 Work build_work(const std::vector<bbe::ReqDesc>& reqs, const std::vector<uint32_t>& state_of,
                 const std::vector<bbe::StartState>& states,
-                const std::vector<uint32_t>& together, int sims_per_item, bool share) {
+                const std::vector<uint32_t>& together, int sims_per_item) {
     Work w;
     struct Share {
         uint64_t rests = 0, over = 0;  // requests with a rest, simulations of the rests
-        uint32_t open = UINT32_MAX;    // the group's item that is not full yet
+        uint64_t at = 0;               // of its next lane in the lane table
         double ticks = -1.0;           // expected
+        bool made = false;             // its items of shared waves
+        bool shared() const { return (over + 63) / 64 < rests; }
     };
     std::vector<Share> shares(reqs.size());  // at a group's number
     for (size_t r = 0; r < reqs.size(); ++r) {
-        shares[together[r]].rests += reqs[r].n_sims % 64 != 0;
-        shares[together[r]].over += reqs[r].n_sims % 64;
+        Share& sh = shares[together[r]];
+        sh.rests += reqs[r].n_sims % 64 != 0;
+        sh.over += reqs[r].n_sims % 64;
+        // every request of a group starts from the same state
+        if (sh.ticks < 0.0) sh.ticks = expected_ticks(reqs[r], states[state_of[r]]);
     }
-    // (paced, expected work) per item: plain items first, each launch's items
-    // largest first (competitor-steps: ticks x competitors x sims)
-    struct Item {
-        bool paced;
-        double work;
-        bbe::Chunk c;
+    // a group's lanes next to each other
+    uint64_t lanes = 0;
+    for (Share& sh : shares) {
+        sh.at = lanes;
+        if (sh.shared()) lanes += sh.over;
+    }
+    std::vector<Item> items, alone;
+    auto add = [&](std::vector<Item>& to, const Share& sh, size_t r, uint64_t first, uint64_t end,
+                   uint32_t flags) {
+        const bbe::ReqDesc& rq = reqs[r];
+        const uint32_t n = (uint32_t)rq.rc.n;
+        for (; first < end; first += (uint64_t)sims_per_item) {
+            const uint32_t count =
+                (uint32_t)std::min<uint64_t>((uint64_t)sims_per_item, end - first);
+            // expected competitor-steps: ticks x competitors x simulations
+            to.push_back({Item::place(rq.pace.paced != 0, sh.ticks * n * count),
+                          {(uint32_t)r, (uint32_t)first, count, n | flags}});
+        }
     };
-    std::vector<Item> items;
-    std::vector<std::pair<uint32_t, uint32_t>> rests;  // group, request
+    for (size_t r = 0; r < reqs.size(); ++r) {
+        const uint32_t n_sims = reqs[r].n_sims;
+        Share& sh = shares[together[r]];
+        add(items, sh, r, 0, sh.shared() ? n_sims - n_sims % 64 : n_sims, 0u);
+        if (lanes) add(alone, sh, r, 0, n_sims, 0u);
+        if (sh.shared() && !sh.made) add(items, sh, r, sh.at, sh.at + sh.over, bbe::kChunkLanes);
+        sh.made = true;
+    }
+    w.n_chunks = items.size() + alone.size();
+    w.size = w.n_chunks * sizeof(bbe::Chunk) + lanes * sizeof(bbe::PackLane);
+    w.bytes.reset(new char[w.size]);
+    bbe::Chunk* chunks = reinterpret_cast<bbe::Chunk*>(w.bytes.get());
+    w.groups = put_items(items, chunks, 0);
+    // the same launches, one for the plain races and one for the paced
+    const std::vector<Group> apart = lanes ? put_items(alone, chunks, items.size()) : w.groups;
+    for (size_t g = 0; g < w.groups.size(); ++g) {
+        w.groups[g].alone_first = apart[g].first;
+        w.groups[g].alone_count = apart[g].count;
+    }
+    bbe::PackLane* table = reinterpret_cast<bbe::PackLane*>(chunks + w.n_chunks);
     for (size_t r = 0; r < reqs.size(); ++r) {
         const bbe::ReqDesc& rq = reqs[r];
         Share& sh = shares[together[r]];
-        if (sh.ticks < 0.0) sh.ticks = expected_ticks(rq, states[state_of[r]]);
-        const bool shared = share && (sh.over + 63) / 64 < sh.rests;
-        const uint64_t own = shared ? rq.n_sims - rq.n_sims % 64 : rq.n_sims;
-        const uint32_t n = (uint32_t)rq.rc.n;
-        for (uint64_t first = 0; first < own; first += (uint64_t)sims_per_item) {
-            const uint32_t count =
-                (uint32_t)std::min<uint64_t>((uint64_t)sims_per_item, own - first);
-            items.push_back({rq.pace.paced != 0, sh.ticks * n * count,
-                             {(uint32_t)r, (uint32_t)first, count, n}});
-        }
-        if (own < rq.n_sims) rests.push_back({together[r], (uint32_t)r});
-    }
-    // a group's requests next to each other
-    std::stable_sort(rests.begin(), rests.end(),
-                     [](const auto& a, const auto& b) { return a.first < b.first; });
-    for (const auto& [group, r] : rests) {
-        const bbe::ReqDesc& rq = reqs[r];
-        Share& sh = shares[group];
-        const uint32_t n = (uint32_t)rq.rc.n;
-        for (uint32_t k = rq.n_sims - rq.n_sims % 64; k < rq.n_sims; ++k) {
-            if (sh.open == UINT32_MAX || items[sh.open].c.count >= (uint32_t)sims_per_item) {
-                sh.open = (uint32_t)items.size();
-                items.push_back({rq.pace.paced != 0, 0.0,
-                                 {r, (uint32_t)w.lanes.size(), 0u, n | bbe::kChunkLanes}});
-            }
-            Item& it = items[sh.open];
-            it.c.count += 1;
-            it.work = sh.ticks * n * it.c.count;
-            w.lanes.push_back({r, rq.sim_begin + k});
-        }
-    }
-    std::stable_sort(items.begin(), items.end(), [](const Item& a, const Item& b) {
-        if (a.paced != b.paced) return !a.paced;
-        return a.work > b.work;
-    });
-    w.chunks.reserve(items.size());
-    for (const Item& it : items) {
-        if (w.groups.empty() || w.groups.back().paced != it.paced)
-            w.groups.push_back({(uint32_t)w.chunks.size(), 0u, it.paced});
-        w.groups.back().count += 1;
-        w.chunks.push_back(it.c);
+        if (!sh.shared()) continue;
+        for (uint32_t k = rq.n_sims - rq.n_sims % 64; k < rq.n_sims; ++k)
+            table[sh.at++] = {(uint32_t)r, rq.sim_begin + k};
     }
     return w;
 }
@@ -310,27 +340,18 @@ int size_class(size_t n_chunks) {
 
 }  // namespace
 
-// A work list on the device and its captured launch sequence.
-struct Sequence {
-    char* d_work = nullptr;  // the work items, then their lane table
-    size_t work_cap = 0;     // bytes
-    uint32_t n_chunks = 0;
-    std::vector<Group> groups;
-    std::vector<int> grids;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-};
-
 struct bbe_batch_plan {
     int device = 0;
     int n_reqs = 0;
     bbe::ReqDesc* d_reqs = nullptr;  // the requests, then their states (host_states)
     uint32_t* d_queue = nullptr;  // one work-queue head per group
-    // requests share waves in `shared` and do not in `alone`, which is made
-    // when the states first call for it (see state_runs)
-    Sequence shared, alone;
-    bool apart = false;  // launch `alone`
+    char* d_work = nullptr;  // the work items (both lists), then the lane table
+    size_t work_cap = 0;     // bytes
+    size_t n_chunks = 0;     // of both lists
+    std::vector<Group> groups;
+    std::vector<int> grids;
     uint64_t shared_gens = 0, alone_gens = 0;
+    uint64_t slots = 0;  // waves of a launch that are resident at once
     uint32_t k0 = 0, k1 = 0;
     unsigned long long* wins = nullptr;
     double* probs = nullptr;
@@ -338,52 +359,71 @@ struct bbe_batch_plan {
     Shape shape{1, 64, 1};
     int item_sims = 64;  // simulations per work item in use (>= shape.sims_per_item)
     hipStream_t cap_stream = nullptr;
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
     std::vector<bbe::ReqDesc> host_reqs;
     std::vector<uint32_t> together;
-    std::vector<char> host_states;  // each request's state's number, then the states
-    size_t states_used = 0;         // bytes
+    // whether the requests run apart (u32, the launch reads it where it runs),
+    // each request's state's number from kStateOf on, then the states
+    std::vector<char> host_states;
+    size_t states_used = 0;  // bytes
 };
 
 namespace {
 
-size_t states_at(int n_reqs) { return ((size_t)n_reqs * sizeof(uint32_t) + 63) / 64 * 64; }
+constexpr size_t kStateOf = 16;
+size_t states_at(int n_reqs) {
+    return (kStateOf + (size_t)n_reqs * sizeof(uint32_t) + 63) / 64 * 64;
+}
 
 char* d_states(const bbe_batch_plan* p) {
     return reinterpret_cast<char*>(p->d_reqs + p->n_reqs);
 }
 
-void keep_states(bbe_batch_plan* p, const std::vector<uint32_t>& state_of,
+bool runs_apart(const bbe_batch_plan* p) {
+    uint32_t apart;
+    std::memcpy(&apart, p->host_states.data(), sizeof apart);
+    return apart != 0;
+}
+
+void keep_states(bbe_batch_plan* p, bool runs_apart, const std::vector<uint32_t>& state_of,
                  const std::vector<bbe::StartState>& states) {
     const size_t at = states_at(p->n_reqs);
+    const uint32_t apart = runs_apart;
     p->host_states.resize(at + (size_t)p->n_reqs * sizeof(bbe::StartState));
-    std::memcpy(p->host_states.data(), state_of.data(), (size_t)p->n_reqs * sizeof(uint32_t));
+    std::memcpy(p->host_states.data(), &apart, sizeof apart);
+    std::memcpy(p->host_states.data() + kStateOf, state_of.data(),
+                (size_t)p->n_reqs * sizeof(uint32_t));
     std::memcpy(p->host_states.data() + at, states.data(),
                 states.size() * sizeof(bbe::StartState));
     p->states_used = at + states.size() * sizeof(bbe::StartState);
 }
 
-hipError_t enqueue(bbe_batch_plan* p, const Sequence& q, hipStream_t s) {
+hipError_t enqueue(bbe_batch_plan* p, hipStream_t s) {
     hipError_t e;
     if ((e = bbe::launch_zero_u64(p->wins, p->n_reqs * bbe::kMaxN, s)) != hipSuccess) return e;
     if (p->steps && (e = bbe::launch_zero_u64(p->steps, 1, s)) != hipSuccess) return e;
-    if ((e = bbe::launch_fill_u32(p->d_queue, 0u, (int)q.groups.size(), s)) != hipSuccess)
+    if ((e = bbe::launch_fill_u32(p->d_queue, 0u, (int)p->groups.size(), s)) != hipSuccess)
         return e;
-    for (size_t g = 0; g < q.groups.size(); ++g) {
-        const Group& gr = q.groups[g];
+    const bbe::Chunk* chunks = reinterpret_cast<const bbe::Chunk*>(p->d_work);
+    for (size_t g = 0; g < p->groups.size(); ++g) {
+        const Group& gr = p->groups[g];
         bbe::BatchArgs a;
         a.reqs = p->d_reqs;
-        a.chunks = reinterpret_cast<const bbe::Chunk*>(q.d_work) + gr.first;
+        a.chunks = chunks + gr.first;
         a.n_chunks = gr.count;
-        a.state_of = reinterpret_cast<const uint32_t*>(d_states(p));
+        a.alone = chunks + gr.alone_first;
+        a.n_alone = gr.alone_count;
+        a.apart = reinterpret_cast<const uint32_t*>(d_states(p));
+        a.state_of = reinterpret_cast<const uint32_t*>(d_states(p) + kStateOf);
         a.states = reinterpret_cast<const bbe::StartState*>(d_states(p) + states_at(p->n_reqs));
-        a.lanes = reinterpret_cast<const bbe::PackLane*>(q.d_work +
-                                                         q.n_chunks * sizeof(bbe::Chunk));
+        a.lanes = reinterpret_cast<const bbe::PackLane*>(chunks + p->n_chunks);
         a.queue = p->d_queue + g;
         a.wins = p->wins;
         a.steps = p->steps;
         a.k0 = p->k0;
         a.k1 = p->k1;
-        if ((e = bbe::launch_batch_mc(a, p->shape.waves_per_block, q.grids[g], gr.paced, s)) !=
+        if ((e = bbe::launch_batch_mc(a, p->shape.waves_per_block, p->grids[g], gr.paced, s)) !=
             hipSuccess)
             return e;
     }
@@ -424,29 +464,25 @@ int item_sims(const std::vector<bbe::ReqDesc>& reqs, int sims_per_item) {
     return (int)std::max<uint64_t>((uint64_t)sims_per_item, 64u * min_gens);
 }
 
-// Puts a work list on the device.
-int upload_work(bbe_batch_plan* p, Sequence& q, const Shape& sh,
-                const std::vector<bbe::ReqDesc>& reqs, const std::vector<uint32_t>& state_of,
+// Puts the work lists on the device.
+int upload_work(bbe_batch_plan* p, const Shape& sh, const std::vector<bbe::ReqDesc>& reqs,
+                const std::vector<uint32_t>& state_of,
                 const std::vector<bbe::StartState>& states) {
     const int per_item = item_sims(reqs, sh.sims_per_item);
-    Work w = build_work(reqs, state_of, states, p->together, per_item, &q == &p->shared);
-    const size_t items = w.chunks.size() * sizeof(bbe::Chunk);
-    std::vector<char> h(items + w.lanes.size() * sizeof(bbe::PackLane));
-    std::memcpy(h.data(), w.chunks.data(), items);
-    if (!w.lanes.empty()) std::memcpy(h.data() + items, w.lanes.data(), h.size() - items);
-    if (h.size() > q.work_cap) {
-        if (q.d_work) (void)hipFree(q.d_work);
-        q.d_work = nullptr;
-        q.work_cap = 0;
-        if (dev_alloc(&q.d_work, h.size()) != hipSuccess)
+    const Work w = build_work(reqs, state_of, states, p->together, per_item);
+    if (w.size > p->work_cap) {
+        if (p->d_work) (void)hipFree(p->d_work);
+        p->d_work = nullptr;
+        p->work_cap = 0;
+        if (dev_alloc(&p->d_work, w.size) != hipSuccess)
             return fail(BBE_ENOMEM, "device allocation of the work list failed");
-        q.work_cap = h.size();
+        p->work_cap = w.size;
     }
-    hipError_t e = BBE_HIP(hipMemcpy(q.d_work, h.data(), h.size(), hipMemcpyHostToDevice));
+    hipError_t e = BBE_HIP(hipMemcpy(p->d_work, w.bytes.get(), w.size, hipMemcpyHostToDevice));
     if (e != hipSuccess) return hip_fail(e, "copying the work list");
-    q.n_chunks = (uint32_t)w.chunks.size();
-    q.groups = w.groups;
-    q.grids.clear();
+    p->n_chunks = w.n_chunks;
+    p->groups = w.groups;
+    p->grids.clear();
     p->shape = sh;
     p->item_sims = per_item;
     const int cus = device_cus();
@@ -456,57 +492,30 @@ int upload_work(bbe_batch_plan* p, Sequence& q, const Shape& sh,
         long cap = std::max(1L, (long)bbe::batch_blocks_per_cu(sh.waves_per_block, g.paced) /
                                     sh.cu_share) *
                    cus;
-        long need = ((long)g.count + sh.waves_per_block - 1) / sh.waves_per_block;
-        q.grids.push_back((int)std::max(1L, std::min(cap, need)));
+        long need = ((long)std::max(g.count, g.alone_count) + sh.waves_per_block - 1) /
+                    sh.waves_per_block;
+        p->grids.push_back((int)std::max(1L, std::min(cap, need)));
+        p->slots = (uint64_t)cap * (uint64_t)sh.waves_per_block;
     }
     return BBE_OK;
 }
 
 // Captures clear -> queue reset -> persistent kernel -> probabilities.
-int capture(bbe_batch_plan* p, Sequence& q) {
+int capture(bbe_batch_plan* p) {
     hipError_t e;
     if ((e = BBE_HIP(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal))) !=
         hipSuccess)
         return hip_fail(e, "beginning graph capture");
-    hipError_t ee = enqueue(p, q, p->cap_stream);
-    e = hipStreamEndCapture(p->cap_stream, &q.graph);
+    hipError_t ee = enqueue(p, p->cap_stream);
+    e = hipStreamEndCapture(p->cap_stream, &p->graph);
     if (ee != hipSuccess || e != hipSuccess)
         return hip_fail(ee != hipSuccess ? ee : e, "capturing the launch sequence");
-    if ((e = BBE_HIP(hipGraphInstantiate(&q.exec, q.graph, nullptr, nullptr, 0))) != hipSuccess)
+    if ((e = BBE_HIP(hipGraphInstantiate(&p->exec, p->graph, nullptr, nullptr, 0))) != hipSuccess)
         return hip_fail(e, "instantiating the graph");
     return BBE_OK;
 }
 
-void release(Sequence& q) {
-    if (q.exec) (void)hipGraphExecDestroy(q.exec);
-    if (q.graph) (void)hipGraphDestroy(q.graph);
-    if (q.d_work) (void)hipFree(q.d_work);
-    q = Sequence();
-}
-
-// Makes `alone` on the plan's device, also while this thread captures another
-// stream.
-bool make_alone(bbe_batch_plan* p, const std::vector<uint32_t>& state_of,
-                const std::vector<bbe::StartState>& states) {
-    int dev = p->device;
-    (void)hipGetDevice(&dev);
-    if (dev != p->device && hipSetDevice(p->device) != hipSuccess) return false;
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    const bool made =
-        upload_work(p, p->alone, p->shape, p->host_reqs, state_of, states) == BBE_OK &&
-        capture(p, p->alone) == BBE_OK;
-    if (!made) release(p->alone);
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    if (dev != p->device) (void)hipSetDevice(dev);
-    return made;
-}
-
-// The most runs of equal states that the requests of a group are in.  A wave of
-// the shared list goes through its lanes' states one after the other, so
-// `alone` is launched once that may be more generations than it has itself: 10^4
-// requests of one simulation, all of different states, would be 157 waves with 64
-// states each.
+// The most runs of equal states that the requests of a group are in.
 uint64_t state_runs(const std::vector<uint32_t>& together,
                     const std::vector<uint32_t>& state_of) {
     std::vector<uint32_t> last(together.size(), UINT32_MAX), runs(together.size());
@@ -520,14 +529,28 @@ uint64_t state_runs(const std::vector<uint32_t>& together,
     return most;
 }
 
+// Whether the plan's requests should run apart, their states given.  A shared
+// wave goes through its lanes' states one after the other, so with `runs` of
+// them a launch may take as long as `runs` launches of one state: of one
+// generation for as many waves as are resident, and in proportion from there
+// on.  Requests of one race of 20 a third of the way on, us (shared / apart): 64
+// of one simulation in 2 states 900 / 351, in 64 states 16800 / 336; 300 of 7 in
+// 2 states 891 / 417.
+bool better_apart(const bbe_batch_plan* p, const std::vector<uint32_t>& state_of) {
+    if (p->shared_gens == p->alone_gens) return false;
+    return state_runs(p->together, state_of) * std::max(p->shared_gens, p->slots) >
+           std::max(p->alone_gens, p->slots);
+}
+
 void destroy(bbe_batch_plan* p) {
     if (!p) return;
     if (p->d_reqs || p->d_queue) (void)hipDeviceSynchronize();
-    release(p->shared);
-    release(p->alone);
+    if (p->exec) (void)hipGraphExecDestroy(p->exec);
+    if (p->graph) (void)hipGraphDestroy(p->graph);
     if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
     if (p->d_reqs) (void)hipFree(p->d_reqs);
     if (p->d_queue) (void)hipFree(p->d_queue);
+    if (p->d_work) (void)hipFree(p->d_work);
     delete p;
 }
 
@@ -617,7 +640,7 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
         t.state = state_of[i];
         p->together[i] = groups.number(t);
     }
-    keep_states(p, state_of, states.all);
+    keep_states(p, false, state_of, states.all);
     p->k0 = (uint32_t)seed;
     p->k1 = (uint32_t)(seed >> 32);
     p->wins = reinterpret_cast<unsigned long long*>(win_counts);
@@ -687,7 +710,7 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
         (void)hipEventCreate(&ev1);
         if (cands.size() < 2) cands.clear();  // nothing to compare
         for (const Shape& c : cands) {
-            int rc = upload_work(p, p->shared, c, tune, state_of, states.all);
+            int rc = upload_work(p, c, tune, state_of, states.all);
             if (rc != BBE_OK) {
                 (void)hipEventDestroy(ev0);
                 (void)hipEventDestroy(ev1);
@@ -698,7 +721,7 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
             bool okc = true;
             for (int rep = 0; rep < 4 && okc; ++rep) {
                 (void)hipEventRecord(ev0, s);
-                okc = enqueue(p, p->shared, s) == hipSuccess;
+                okc = enqueue(p, s) == hipSuccess;
                 (void)hipEventRecord(ev1, s);
                 (void)hipEventSynchronize(ev1);
                 float ms = 0.0f;
@@ -716,8 +739,8 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
         g_tuned[key] = best;
         store_tune_entry(p->device, key.second, best);
     }
-    int rc = upload_work(p, p->shared, best, p->host_reqs, state_of, states.all);
-    if (rc == BBE_OK) rc = capture(p, p->shared);
+    int rc = upload_work(p, best, p->host_reqs, state_of, states.all);
+    if (rc == BBE_OK) rc = capture(p);
     if (rc != BBE_OK) {
         destroy(p);
         return rc;
@@ -732,16 +755,15 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
 }
 
 BBE_API int bbe_batch_plan_launch(bbe_batch_plan* plan, void* stream) {
-    if (!plan || !plan->shared.exec) return fail(BBE_EINVAL, "plan is NULL");
-    const Sequence& q = plan->apart ? plan->alone : plan->shared;
-    hipError_t e = BBE_HIP(hipGraphLaunch(q.exec, static_cast<hipStream_t>(stream)));
+    if (!plan || !plan->exec) return fail(BBE_EINVAL, "plan is NULL");
+    hipError_t e = BBE_HIP(hipGraphLaunch(plan->exec, static_cast<hipStream_t>(stream)));
     if (e != hipSuccess) return hip_fail(e, "launching the plan graph");
     return ok();
 }
 
 BBE_API int bbe_batch_plan_set_states(bbe_batch_plan* plan, const bbe_state* states,
                                       void* stream) {
-    if (!plan || !plan->shared.exec) return fail(BBE_EINVAL, "plan is NULL");
+    if (!plan || !plan->exec) return fail(BBE_EINVAL, "plan is NULL");
     if (!states) return fail(BBE_EINVAL, "states is NULL");
     const int n_reqs = plan->n_reqs;
     // validate every state before touching the plan; a request in the state of
@@ -763,15 +785,10 @@ BBE_API int bbe_batch_plan_set_states(bbe_batch_plan* plan, const bbe_state* sta
         }
         b = (uint32_t)r;
     }
-    keep_states(plan, state_of, distinct);
+    keep_states(plan, better_apart(plan, state_of), state_of, distinct);
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     (void)hipStreamIsCapturing(s, &cap);
-    plan->apart = plan->shared_gens < plan->alone_gens &&
-                  state_runs(plan->together, state_of) * plan->shared_gens > plan->alone_gens;
-    // `shared` gives the same results where `alone` cannot be made now
-    if (plan->apart && !plan->alone.exec)
-        plan->apart = cap == hipStreamCaptureStatusNone && make_alone(plan, state_of, distinct);
     // ordered after earlier launches on `stream`; the pageable source is
     // consumed before the call returns.  A copy that a graph records takes the
     // whole table, which may hold more states when the graph runs.
@@ -789,11 +806,15 @@ BBE_API int bbe_batch_plan_info(const bbe_batch_plan* plan, int* waves_per_block
     if (waves_per_block) *waves_per_block = plan->shape.waves_per_block;
     if (grid) {
         int g = 0;
-        for (int x : plan->shared.grids) g = std::max(g, x);
+        for (int x : plan->grids) g = std::max(g, x);
         *grid = g;
     }
     if (sims_per_item) *sims_per_item = plan->item_sims;
-    if (n_items) *n_items = (int)plan->shared.n_chunks;
+    if (n_items) {
+        *n_items = 0;
+        for (const Group& g : plan->groups)
+            *n_items += (int)(runs_apart(plan) ? g.alone_count : g.count);
+    }
     return ok();
 }
 

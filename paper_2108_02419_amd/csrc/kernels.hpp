@@ -121,15 +121,18 @@ struct PackLane {
     uint32_t sim;  // its index
 };
 
-// One launch serves the work items chunks[0 .. n_chunks) of every
-// competitor count (chunk.n selects the template instance).
+// One launch serves the work items chunks[0 .. n_chunks) -- or, where the
+// requests run apart, alone[0 .. n_alone) -- of every competitor count (chunk.n
+// selects the template instance).
 struct BatchArgs {
     const ReqDesc* reqs;
     const Chunk* chunks;
+    const Chunk* alone;         // the items where the requests run apart
+    const uint32_t* apart;      // [1]: whether they do; lies with the states
     const uint32_t* state_of;   // [n_reqs]: each request's entry of `states`
     const StartState* states;
     const PackLane* lanes;      // of the items with kChunkLanes
-    uint32_t n_chunks;
+    uint32_t n_chunks, n_alone;
     uint32_t* queue;            // the launch's work-queue head, zeroed before launch
     unsigned long long* wins;   // [n_reqs][kMaxN], zeroed before launch
     unsigned long long* steps;  // [1] or null, zeroed before launch
