@@ -46,6 +46,16 @@ struct Work {
     std::vector<Group> groups;
 };
 
+// A plan's requests.
+struct Requests {
+    const bbe::ReqDesc* at;
+    size_t n;
+    size_t size() const { return n; }
+    const bbe::ReqDesc& operator[](size_t i) const { return at[i]; }
+    const bbe::ReqDesc* begin() const { return at; }
+    const bbe::ReqDesc* end() const { return at + n; }
+};
+
 // Numbers values by their bytes: equal ones get the same number, new ones the
 // next.  Neighbours are compared first, as equal ones mostly come in rows.
 template <class T>
@@ -151,7 +161,7 @@ std::vector<Group> put_items(std::vector<Item>& items, bbe::Chunk* chunks, size_
 // one of a single request.  10^4 requests of 1 to 200 simulations (37 on
 // average) of one race of 20 are 5900 generations instead of 13100; setting
 // their states and launching them took 2.54 ms before and 1.20 ms so.
-Work build_work(const std::vector<bbe::ReqDesc>& reqs, const std::vector<uint32_t>& state_of,
+Work build_work(const Requests& reqs, const std::vector<uint32_t>& state_of,
                 const std::vector<bbe::StartState>& states,
                 const std::vector<uint32_t>& together, int sims_per_item) {
     Work w;
@@ -343,7 +353,7 @@ int size_class(size_t n_chunks) {
 struct bbe_batch_plan {
     int device = 0;
     int n_reqs = 0;
-    bbe::ReqDesc* d_reqs = nullptr;  // the requests, then their states (host_states)
+    bbe::ReqDesc* d_reqs = nullptr;  // as `table`
     uint32_t* d_queue = nullptr;  // one work-queue head per group
     char* d_work = nullptr;  // the work items (both lists), then the lane table
     size_t work_cap = 0;     // bytes
@@ -361,12 +371,12 @@ struct bbe_batch_plan {
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    std::vector<bbe::ReqDesc> host_reqs;
     std::vector<uint32_t> together;
-    // whether the requests run apart (u32, the launch reads it where it runs),
-    // each request's state's number from kStateOf on, then the states
-    std::vector<char> host_states;
-    size_t states_used = 0;  // bytes
+    // the requests, then (at state_part) whether they run apart (u32, the launch
+    // reads it where it runs), each one's state's number from kStateOf on and
+    // from states_at on the states; up to `used` bytes
+    std::vector<char> table;
+    size_t used = 0;
 };
 
 namespace {
@@ -376,27 +386,33 @@ size_t states_at(int n_reqs) {
     return (kStateOf + (size_t)n_reqs * sizeof(uint32_t) + 63) / 64 * 64;
 }
 
-char* d_states(const bbe_batch_plan* p) {
-    return reinterpret_cast<char*>(p->d_reqs + p->n_reqs);
+size_t state_part(const bbe_batch_plan* p) { return (size_t)p->n_reqs * sizeof(bbe::ReqDesc); }
+
+bbe::ReqDesc* host_reqs(bbe_batch_plan* p) {
+    return reinterpret_cast<bbe::ReqDesc*>(p->table.data());
+}
+
+Requests requests(bbe_batch_plan* p) { return {host_reqs(p), (size_t)p->n_reqs}; }
+
+const char* d_states(const bbe_batch_plan* p) {
+    return reinterpret_cast<const char*>(p->d_reqs + p->n_reqs);
 }
 
 bool runs_apart(const bbe_batch_plan* p) {
     uint32_t apart;
-    std::memcpy(&apart, p->host_states.data(), sizeof apart);
+    std::memcpy(&apart, p->table.data() + state_part(p), sizeof apart);
     return apart != 0;
 }
 
 void keep_states(bbe_batch_plan* p, bool runs_apart, const std::vector<uint32_t>& state_of,
                  const std::vector<bbe::StartState>& states) {
-    const size_t at = states_at(p->n_reqs);
+    char* to = p->table.data() + state_part(p);
     const uint32_t apart = runs_apart;
-    p->host_states.resize(at + (size_t)p->n_reqs * sizeof(bbe::StartState));
-    std::memcpy(p->host_states.data(), &apart, sizeof apart);
-    std::memcpy(p->host_states.data() + kStateOf, state_of.data(),
-                (size_t)p->n_reqs * sizeof(uint32_t));
-    std::memcpy(p->host_states.data() + at, states.data(),
-                states.size() * sizeof(bbe::StartState));
-    p->states_used = at + states.size() * sizeof(bbe::StartState);
+    std::memcpy(to, &apart, sizeof apart);
+    std::memcpy(to + kStateOf, state_of.data(), (size_t)p->n_reqs * sizeof(uint32_t));
+    const size_t at = states_at(p->n_reqs), bytes = states.size() * sizeof(bbe::StartState);
+    std::memcpy(to + at, states.data(), bytes);
+    p->used = state_part(p) + at + bytes;
 }
 
 hipError_t enqueue(bbe_batch_plan* p, hipStream_t s) {
@@ -434,14 +450,14 @@ hipError_t enqueue(bbe_batch_plan* p, hipStream_t s) {
 }
 
 // Generations of a batch: ceil(n_sims / 64) per request.
-uint64_t generation_count(const std::vector<bbe::ReqDesc>& reqs) {
+uint64_t generation_count(const Requests& reqs) {
     uint64_t g = 0;
     for (const bbe::ReqDesc& r : reqs) g += (r.n_sims + 63u) / 64u;
     return g;
 }
 
 // The same as build_work makes them, with shared ones counted once.
-uint64_t shared_generation_count(const std::vector<bbe::ReqDesc>& reqs,
+uint64_t shared_generation_count(const Requests& reqs,
                                  const std::vector<uint32_t>& together) {
     std::vector<uint64_t> over(reqs.size());
     uint64_t g = 0;
@@ -458,14 +474,14 @@ uint64_t shared_generation_count(const std::vector<bbe::ReqDesc>& reqs,
 // items: a batch of very large requests gets fewer, longer items instead of
 // a work list of tens of millions.
 constexpr uint64_t kMaxItems = 1u << 20;
-int item_sims(const std::vector<bbe::ReqDesc>& reqs, int sims_per_item) {
+int item_sims(const Requests& reqs, int sims_per_item) {
     const uint64_t gens = generation_count(reqs);
     const uint64_t min_gens = (gens + kMaxItems - 1) / kMaxItems;
     return (int)std::max<uint64_t>((uint64_t)sims_per_item, 64u * min_gens);
 }
 
 // Puts the work lists on the device.
-int upload_work(bbe_batch_plan* p, const Shape& sh, const std::vector<bbe::ReqDesc>& reqs,
+int upload_work(bbe_batch_plan* p, const Shape& sh, const Requests& reqs,
                 const std::vector<uint32_t>& state_of,
                 const std::vector<bbe::StartState>& states) {
     const int per_item = item_sims(reqs, sh.sims_per_item);
@@ -588,7 +604,9 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
     bbe_batch_plan* p = new (std::nothrow) bbe_batch_plan();
     if (!p) return fail(BBE_ENOMEM, "out of host memory");
     p->n_reqs = n_reqs;
-    p->host_reqs.resize(n_reqs);
+    p->table.resize((size_t)n_reqs * (sizeof(bbe::ReqDesc) + sizeof(bbe::StartState)) +
+                    states_at(n_reqs));
+    bbe::ReqDesc* descs = host_reqs(p);
     p->together.resize(n_reqs);
     std::vector<uint32_t> state_of(n_reqs);
     Distinct<bbe::StartState> states((size_t)n_reqs);
@@ -625,10 +643,10 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
             return fail(BBE_EINVAL, "request %d: stop_after = %d outside 0..%d", i,
                         q.stop_after, q.race->n);
         }
-        bbe::ReqDesc& d = p->host_reqs[i];
+        bbe::ReqDesc& d = descs[i];
         fill_desc(q, d);
         if (again && state_of[i] == state_of[i - 1] &&
-            d.stop_after == p->host_reqs[i - 1].stop_after) {
+            d.stop_after == descs[i - 1].stop_after) {
             p->together[i] = p->together[i - 1];
             continue;
         }
@@ -649,16 +667,13 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
     (void)hipGetDevice(&p->device);
 
     hipError_t e;
-    const size_t req_bytes = sizeof(bbe::ReqDesc) * n_reqs;
-    if (dev_alloc(&p->d_reqs, req_bytes + p->host_states.size()) != hipSuccess ||
+    if (dev_alloc(&p->d_reqs, p->table.size()) != hipSuccess ||
         dev_alloc(&p->d_queue, sizeof(uint32_t) * bbe::kMaxN) != hipSuccess) {
         destroy(p);
         return fail(BBE_ENOMEM, "device allocation of the request table failed");
     }
-    if ((e = BBE_HIP(hipMemcpy(p->d_reqs, p->host_reqs.data(), req_bytes,
-                               hipMemcpyHostToDevice))) != hipSuccess ||
-        (e = hipMemcpy(d_states(p), p->host_states.data(), p->states_used,
-                       hipMemcpyHostToDevice)) != hipSuccess) {
+    if ((e = BBE_HIP(hipMemcpy(p->d_reqs, p->table.data(), p->used, hipMemcpyHostToDevice))) !=
+        hipSuccess) {
         destroy(p);
         return hip_fail(e, "copying the request table");
     }
@@ -671,8 +686,8 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
 
     // Launch shape: tuned on this batch, or from the cache, or the default.
     Shape best{1, 64, 1};
-    p->alone_gens = generation_count(p->host_reqs);
-    p->shared_gens = shared_generation_count(p->host_reqs, p->together);
+    p->alone_gens = generation_count(requests(p));
+    p->shared_gens = shared_generation_count(requests(p), p->together);
     const uint64_t work = p->shared_gens;
     std::pair<int, int> key{p->device, size_class(work)};
     bool have = false;
@@ -699,8 +714,8 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
         // more than kTuneGens generations -- on the same requests with their
         // simulation counts scaled down to about that much work.
         constexpr uint64_t kTuneGens = 1u << 16;
-        std::vector<bbe::ReqDesc> tune = p->host_reqs;
-        const uint64_t gens = generation_count(tune);
+        std::vector<bbe::ReqDesc> tune(descs, descs + n_reqs);
+        const uint64_t gens = p->alone_gens;
         if (gens > kTuneGens)
             for (bbe::ReqDesc& r : tune)
                 r.n_sims = (uint32_t)std::max<uint64_t>(1u, (uint64_t)r.n_sims * kTuneGens / gens);
@@ -710,7 +725,7 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
         (void)hipEventCreate(&ev1);
         if (cands.size() < 2) cands.clear();  // nothing to compare
         for (const Shape& c : cands) {
-            int rc = upload_work(p, c, tune, state_of, states.all);
+            int rc = upload_work(p, c, {tune.data(), tune.size()}, state_of, states.all);
             if (rc != BBE_OK) {
                 (void)hipEventDestroy(ev0);
                 (void)hipEventDestroy(ev1);
@@ -739,7 +754,7 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
         g_tuned[key] = best;
         store_tune_entry(p->device, key.second, best);
     }
-    int rc = upload_work(p, best, p->host_reqs, state_of, states.all);
+    int rc = upload_work(p, best, requests(p), state_of, states.all);
     if (rc == BBE_OK) rc = capture(p);
     if (rc != BBE_OK) {
         destroy(p);
@@ -772,7 +787,7 @@ BBE_API int bbe_batch_plan_set_states(bbe_batch_plan* plan, const bbe_state* sta
     std::vector<bbe::StartState> distinct;
     distinct.reserve(n_reqs);
     for (int r = 0; r < n_reqs; ++r) {
-        const bbe::ReqDesc& q = plan->host_reqs[r];
+        const bbe::ReqDesc& q = requests(plan)[r];
         uint32_t& b = before[plan->together[r]];
         if (b != UINT32_MAX && same_state(&states[b], &states[r], q.rc.n)) {
             state_of[r] = state_of[b];
@@ -792,10 +807,10 @@ BBE_API int bbe_batch_plan_set_states(bbe_batch_plan* plan, const bbe_state* sta
     // ordered after earlier launches on `stream`; the pageable source is
     // consumed before the call returns.  A copy that a graph records takes the
     // whole table, which may hold more states when the graph runs.
-    hipError_t e = BBE_HIP(hipMemcpyAsync(
-        d_states(plan), plan->host_states.data(),
-        cap == hipStreamCaptureStatusNone ? plan->states_used : plan->host_states.size(),
-        hipMemcpyHostToDevice, s));
+    const size_t from = state_part(plan);
+    const size_t to = cap == hipStreamCaptureStatusNone ? plan->used : plan->table.size();
+    hipError_t e = BBE_HIP(hipMemcpyAsync(plan->d_reqs + n_reqs, plan->table.data() + from,
+                                          to - from, hipMemcpyHostToDevice, s));
     if (e != hipSuccess) return hip_fail(e, "copying the request table");
     return ok();
 }
