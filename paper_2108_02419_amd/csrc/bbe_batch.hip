@@ -56,9 +56,26 @@ struct Requests {
     const bbe::ReqDesc* end() const { return at + n; }
 };
 
-// Numbers values by their bytes: equal ones get the same number, new ones the
-// next.  Neighbours are compared first, as equal ones mostly come in rows.
+// Hash of a value's bytes: sums of products of neighbouring words, each with a
+// constant of its own added (NH of Black, Halevi, Krawczyk, Krovetz and Rogaway's
+// UMAC), which the compiler does several at a time.
 template <class T>
+uint64_t hash_of(const T& v) {
+    constexpr size_t words = sizeof(T) / 4;
+    static_assert(sizeof(T) % 4 == 0);
+    uint32_t w[words + 1];
+    std::memcpy(w, &v, sizeof v);
+    w[words] = 0;
+    uint64_t sum = 0;
+    uint32_t k = 0x9E3779B9u;
+    for (size_t i = 0; i < words; i += 2, k += 0x9E3779B9u)
+        sum += (uint64_t)(w[i] + k) * (w[i + 1] + (k ^ 0x85EBCA6Bu));
+    sum *= 0x9E3779B97F4A7C15ull;
+    return sum ^ (sum >> 32);
+}
+
+// Finds equal ones among numbered values: find(hash, number, equal) gives the
+// first number put in for which equal(it) holds, else puts this one in.
 class Distinct {
   public:
     explicit Distinct(size_t n) {
@@ -66,42 +83,16 @@ class Distinct {
         while (cap < 2 * n) cap *= 2;
         slots_.assign(cap, UINT32_MAX);
     }
-    uint32_t number(const T& v) {
-        if (!all.empty() && std::memcmp(&all[last_], &v, sizeof(T)) == 0) return last_;
-        for (size_t i = hash(v) & (slots_.size() - 1);; i = (i + 1) & (slots_.size() - 1)) {
-            if (slots_[i] == UINT32_MAX) {
-                slots_[i] = (uint32_t)all.size();
-                all.push_back(v);
-            }
-            if (std::memcmp(&all[slots_[i]], &v, sizeof(T)) == 0) return last_ = slots_[i];
+    template <class Equal>
+    uint32_t find(uint64_t hash, uint32_t number, const Equal& equal) {
+        for (size_t i = hash & (slots_.size() - 1);; i = (i + 1) & (slots_.size() - 1)) {
+            if (slots_[i] == UINT32_MAX) return slots_[i] = number;
+            if (equal(slots_[i])) return slots_[i];
         }
     }
-    std::vector<T> all;
 
   private:
-    static uint64_t hash(const T& v) {
-        static_assert(sizeof(T) % 8 == 0);
-        // four chains of products at a time, as each waits on its last
-        uint64_t h[4] = {1, 2, 3, 4};
-        for (size_t i = 0; i < sizeof(T); i += 8) {
-            uint64_t w;
-            std::memcpy(&w, reinterpret_cast<const char*>(&v) + i, 8);
-            uint64_t& x = h[i / 8 % 4];
-            x = (x ^ w) * 0x9E3779B97F4A7C15ull;
-            x ^= x >> 32;
-        }
-        return h[0] ^ (h[1] >> 7) ^ (h[2] >> 13) ^ (h[3] >> 19);
-    }
     std::vector<uint32_t> slots_;
-    uint32_t last_ = 0;
-};
-
-// What the simulations that share a wave have in common.
-struct Together {
-    bbe::RaceConst rc;
-    bbe::RacePace pace;
-    int stop_after;
-    uint32_t state;
 };
 
 // Expected ticks until the request's simulations end (used only to order
@@ -155,7 +146,7 @@ std::vector<Group> put_items(std::vector<Item>& items, bbe::Chunk* chunks, size_
 // The work list, and behind it the items of the list without shared waves.
 //
 // Requests that differ in nothing but their simulations (together[r], the
-// number of r's group, is the same) share waves: what is left of each after
+// first one of r's group, is the same) share waves: what is left of each after
 // whole generations of 64 goes to the lane table, request after request.
 // That is done where it saves a generation: a shared one takes no longer than
 // one of a single request.  10^4 requests of 1 to 200 simulations (37 on
@@ -172,7 +163,7 @@ Work build_work(const Requests& reqs, const std::vector<uint32_t>& state_of,
         bool made = false;             // its items of shared waves
         bool shared() const { return (over + 63) / 64 < rests; }
     };
-    std::vector<Share> shares(reqs.size());  // at a group's number
+    std::vector<Share> shares(reqs.size());  // at a group's first request
     for (size_t r = 0; r < reqs.size(); ++r) {
         Share& sh = shares[together[r]];
         sh.rests += reqs[r].n_sims % 64 != 0;
@@ -609,8 +600,8 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
     bbe::ReqDesc* descs = host_reqs(p);
     p->together.resize(n_reqs);
     std::vector<uint32_t> state_of(n_reqs);
-    Distinct<bbe::StartState> states((size_t)n_reqs);
-    Distinct<Together> groups((size_t)n_reqs);
+    std::vector<bbe::StartState> states;
+    Distinct same_states((size_t)n_reqs), groups((size_t)n_reqs);
     for (int i = 0; i < n_reqs; ++i) {
         const bbe_request& q = reqs[i];
         // a row of requests of one race from one state is looked at once
@@ -623,8 +614,13 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
             std::memset(&st, 0, sizeof st);
             rc = q.race ? check_state(q.race, q.state, st.d0, st.s0, st.id0, &st.t0)
                         : fail(BBE_EINVAL, "request %d: race is NULL", i);
-            if (rc == BBE_OK) state_of[i] = states.number(st);
-            else if (q.race) rc = fail(rc, "request %d: %s", i, g_err.c_str());
+            if (rc == BBE_OK) {
+                const uint32_t at = (uint32_t)states.size();
+                state_of[i] = same_states.find(hash_of(st), at, [&](uint32_t k) {
+                    return std::memcmp(&states[k], &st, sizeof st) == 0;
+                });
+                if (state_of[i] == at) states.push_back(st);
+            } else if (q.race) rc = fail(rc, "request %d: %s", i, g_err.c_str());
         }
         if (rc != BBE_OK) {
             destroy(p);
@@ -650,15 +646,15 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
             p->together[i] = p->together[i - 1];
             continue;
         }
-        Together t;
-        std::memset(&t, 0, sizeof t);
-        t.rc = d.rc;
-        t.pace = d.pace;
-        t.stop_after = d.stop_after;
-        t.state = state_of[i];
-        p->together[i] = groups.number(t);
+        const uint64_t hash = hash_of(d.rc) + 31u * hash_of(d.pace) +
+                              ((uint64_t)state_of[i] << 5) + (uint64_t)d.stop_after;
+        p->together[i] = groups.find(hash, (uint32_t)i, [&](uint32_t k) {
+            return state_of[k] == state_of[i] && descs[k].stop_after == d.stop_after &&
+                   std::memcmp(&descs[k].rc, &d.rc, sizeof d.rc) == 0 &&
+                   std::memcmp(&descs[k].pace, &d.pace, sizeof d.pace) == 0;
+        });
     }
-    keep_states(p, false, state_of, states.all);
+    keep_states(p, false, state_of, states);
     p->k0 = (uint32_t)seed;
     p->k1 = (uint32_t)(seed >> 32);
     p->wins = reinterpret_cast<unsigned long long*>(win_counts);
@@ -725,7 +721,7 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
         (void)hipEventCreate(&ev1);
         if (cands.size() < 2) cands.clear();  // nothing to compare
         for (const Shape& c : cands) {
-            int rc = upload_work(p, c, {tune.data(), tune.size()}, state_of, states.all);
+            int rc = upload_work(p, c, {tune.data(), tune.size()}, state_of, states);
             if (rc != BBE_OK) {
                 (void)hipEventDestroy(ev0);
                 (void)hipEventDestroy(ev1);
@@ -754,7 +750,7 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
         g_tuned[key] = best;
         store_tune_entry(p->device, key.second, best);
     }
-    int rc = upload_work(p, best, requests(p), state_of, states.all);
+    int rc = upload_work(p, best, requests(p), state_of, states);
     if (rc == BBE_OK) rc = capture(p);
     if (rc != BBE_OK) {
         destroy(p);

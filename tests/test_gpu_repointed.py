@@ -111,3 +111,25 @@ def test_captured_repointing(torch, orc):
     together = [pool[3]] * 40
     c.plan.set_states(*_arrays(together))
     c.expect(together, "one state again")
+
+
+def test_requests_are_grouped_by_value(torch, orc):
+    """Handles of equal races share waves; races that differ in one value of one
+    competitor, or in the time term, do not."""
+    rng = np.random.default_rng(4)
+    base = inputs.pace_params(rng, inputs.competitor_params(rng, 6))
+    comps = [base, base.copy()]
+    for col in range(7):
+        comps.append(base.copy())
+        comps[-1][5, col] *= np.float32(0.99) if col != 6 else np.float32(0.5)
+    comps[-1][5, 6] = np.floor(comps[-1][5, 6])
+    specs = [(Race(c, L), None, 0, 3, 40 + i, 0) for i, c in enumerate(comps)]
+    wins = torch.zeros((len(specs), 20), dtype=torch.int64, device="cuda")
+    plan = BatchPlan(specs, SEED, wins, None, None, autotune=False)
+    announce("nine races, two of them equal")
+    assert plan.info()["n_items"] == len(specs) - 1
+    plan.launch()
+    torch.cuda.synchronize()
+    for i, c in enumerate(comps):
+        _, ow, _ = orc.race_sim(c, L, 3, SEED, request=40 + i, want_orders=False)
+        np.testing.assert_array_equal(wins[i, :6].cpu().numpy().astype(np.uint64), ow)
