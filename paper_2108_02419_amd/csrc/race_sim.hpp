@@ -6,10 +6,7 @@
 // NaN position).  Slot k holds the position d[k], the LDS byte offset
 // rec[k] of its competitor's parameter record (pbase + 16 * competitor
 // index; it also locates the competitor's draw) and the previous step s[k].
-// Slots are ordered by the 64-bit key (bits(d) << 32) | rec: non-negative
-// floats, +inf and the parking NaN order like their bit patterns, and rec
-// grows with the competitor index, so this is (position, index) order.  The
-// competitor ahead of slot k is then the first slot above it with a larger
+// The competitor ahead of slot k is then the first slot above it with a larger
 // position -- slot k+1 unless positions are equal -- and the query of Eq. 1
 // costs O(1) per competitor instead of a scan over all pairs.
 //
@@ -19,24 +16,25 @@
 //      competitor c takes word (c>>1)&3 of block c>>3, its high half for
 //      even c and its low half for odd c, as the integer k (u = k * 2^-16);
 //      the draws go to the lane's column of an LDS table and each slot
-//      reads the draw of its own competitor;
+//      reads the draw of its own competitor (write_draws, SlotInputs);
 //   2. competitor ahead: the running competitor with the smallest position
 //      greater than d_c (lowest index among equal positions); gap =
 //      fl(d_ahead - d_c), +inf if nobody is ahead;
 //   3. Eq. 1: R = alpha + beta*d (+ gamma*min(t, tau) in the paced
 //      variants); free: S = R*(elo + espan*u); blocked (gap <= theta):
 //      S = R*min(s_c, s_ahead);
-//   4. synchronous update d += S, s = S of the running competitors; a
-//      competitor whose new position reaches L crosses the line;
-//   5. this tick's finishers are ranked after the earlier ones, among
-//      themselves by the fraction fl((L - d_old)/S), then by index, and are
-//      parked (position NaN: every comparison with it is false, so a parked
-//      slot never crosses again and is never "ahead" of anyone);
-//   6. compare-exchange passes, alternately upward and downward, restore the
-//      slot order.
+//   4. synchronous update d += S, s = S of the running competitors
+//      (slots_tick_plain, slots_tick_tied), and the slots' order restored
+//      (slots_sort);
+//   5. a competitor whose position has reached L has crossed the line and is
+//      parked (slots_cross; position NaN: every comparison with it is false, so
+//      a parked slot never crosses again and is never "ahead" of anyone); this
+//      tick's finishers are ranked after the earlier ones, among themselves by
+//      the fraction fl((L - d_old)/S), then by index (slots_rank).
 //
-// slots_tick does this in full.  The Monte-Carlo kernels use it only where two
-// positions are equal, and slots_tick_plain (below) everywhere else.
+// Ticks come in three kinds, each a loop of its own (run_generation): open ones,
+// in which nobody can reach the line (no step 5), plain ones, and those in which
+// some lane has equal positions.
 #pragma once
 
 #include "race_common.hpp"
@@ -181,229 +179,21 @@ __device__ __forceinline__ void write_draws(uint32_t ucol, uint32_t t, uint32_t 
     }
 }
 
-// Steps 1-4 for one lane.  `ucol` is the byte offset of this lane's column
-// of the draw table (competitor c's draw at ucol + 256*c), `pbase` that of
-// the parameter records.  Returns the bit mask of slots that crossed the
-// line (their position still holds the start-of-tick value; their s holds
-// the step S that took them over).  kPace selects how the time term of R
-// is added (with gamma = 0 it adds +0, so every mode agrees on unpaced
-// races).  A parked slot's step changes nothing: it stays parked and is never
-// ahead of anyone.
-template <int N, Pace kPace = kPaceOff>
-__device__ __forceinline__ uint32_t slots_tick(Slots<N>& sl, uint32_t ucol,
-                                               uint32_t pbase, float L, uint32_t t,
-                                               uint32_t sim, uint32_t request, uint32_t k0,
-                                               uint32_t k1) {
-    if constexpr (kPace == kPaceTable) {
-        write_pace_terms<N>(pbase, t);
-    }
-    // 1. draws, competitor order, into this lane's column
-    write_draws<N>(ucol, t, sim, request, k0, k1);
-
-    // 2.-4. Slots from the top down.  Slots are in (position, index) order,
-    //    so the competitor ahead of slot k is the first slot above it with a
-    //    larger position: slot k+1, or -- where positions are equal -- the
-    //    one found for slot k+1, carried down in (nd, ns).  The start-of-tick
-    //    position and step of slot k+1 are kept in (d_up, s_up) because the
-    //    update overwrites the slot (synchronous update).  The draw of
-    //    competitor c sits at ucol + 256*c = ubias + 16*rec; each slot's draw
-    //    and parameter record are read from LDS kPf slots ahead of use.
-    const uint32_t ubias = ucol - 16u * pbase;
-    constexpr int kPf = 4;
-    float pu[N], pth[N], pga[N];
-    f32x4 pp[N];
-#pragma unroll
-    for (int k = N - 1; k >= 0 && k >= N - kPf; --k) {
-        const uint32_t rec = sl.rec[k];
-        pu[k] = lds_ld<float>(ubias + (rec << 4));
-        pp[k] = lds_ld<f32x4>(rec);
-        if constexpr (kPace == kPaceTable) {
-            const f32x2 q = lds_ld<f32x2>(rec + kRecHalf<N>);
-            pth[k] = q.x;
-            pga[k] = q.y;  // the term itself
-        } else {
-            pth[k] = lds_ld<float>(rec + kRecHalf<N>);
-        }
-    }
-    float nd = __builtin_inff(), ns = 0.0f;
-    float d_up = __builtin_inff(), s_up = 0.0f;
-    uint32_t cross = 0;
-#pragma unroll
-    for (int k = N - 1; k >= 0; --k) {
-        if (k - kPf >= 0) {
-            const uint32_t rec = sl.rec[k - kPf];
-            pu[k - kPf] = lds_ld<float>(ubias + (rec << 4));
-            pp[k - kPf] = lds_ld<f32x4>(rec);
-            if constexpr (kPace == kPaceTable) {
-                const f32x2 q = lds_ld<f32x2>(rec + kRecHalf<N>);
-                pth[k - kPf] = q.x;
-                pga[k - kPf] = q.y;
-            } else {
-                pth[k - kPf] = lds_ld<float>(rec + kRecHalf<N>);
-            }
-        }
-        const float d = sl.d[k];
-        const float s = sl.s[k];
-        const bool gt = d_up > d;  // false next to a parked (NaN) slot
-        nd = gt ? d_up : nd;
-        ns = gt ? s_up : ns;
-        // Eq. 1
-        const f32x4 p = pp[k];
-        float R = p.z + p.w * d;
-        if constexpr (kPace == kPaceTable) R = R + pga[k];
-        float x = p.x + p.y * pu[k];
-        // min of two positive steps (ns = 0 only when nobody is ahead)
-        float s_min = __uint_as_float(min(__float_as_uint(s), __float_as_uint(ns)));
-        float gap = nd - d;  // +inf when nobody is ahead
-        // R*s_min when blocked, R*x when free (one product of the selected
-        // factor rounds exactly as the product taken in that branch)
-        float S = R * ((gap <= pth[k]) ? s_min : x);
-        // synchronous update; a parked slot computes NaN and stays parked
-        float dn = d + S;
-        bool cr = dn >= L;
-        cross = cross + cross + (cr ? 1u : 0u);  // slot k lands on bit k
-        sl.d[k] = cr ? d : dn;
-        sl.s[k] = S;
-        d_up = d;
-        s_up = s;
-    }
-    return cross;
-}
-
-// Step 5: ranks this tick's finishers (slot mask `cross`) after the `nfin`
-// earlier ones, records them, and parks every crossing slot (position NaN);
-// returns the number ranked.  `rank` is false in lanes whose simulation has
-// already ended: their finishers are parked but not recorded.  In one pass
-// over the crossing slots, each finisher is compacted -- entry j (the j-th
-// set bit of `cross`) holds its competitor index in the lane's column of a
-// byte table, at icol + 64*j, and, when there are several, its crossing
-// fraction in the lane's (already consumed) column of the draw table, at
-// ucol + 256*j -- and its slot is parked.  The entries are then picked in
-// (fraction, index) order by a selection over those c entries, so the work
-// grows with c^2 for the few finishers of a tick rather than with c*N.
-template <int N, class Win>
-__device__ __forceinline__ int slots_rank_park(Slots<N>& sl, uint32_t cross, bool rank, float L,
-                                               uint32_t ucol, uint32_t icol, uint32_t pbase,
-                                               int nfin, const Win& win, uint32_t row) {
-    const int c = __builtin_popcount(cross);
-#pragma unroll
-    for (int k = 0; k < N; ++k)
-        if ((cross >> k) & 1u) {
-            if (rank) {
-                const uint32_t j = __builtin_popcount(cross & ((1u << k) - 1u));
-                lds_st<uint8_t>(icol + 64u * j, (uint8_t)((sl.rec[k] - pbase) >> 4));
-                // a lone finisher needs no fraction
-                if (c > 1) lds_st<float>(ucol + 256u * j, (L - sl.d[k]) / sl.s[k]);
-            }
-            sl.d[k] = parked();
-        }
-    if (!rank) return 0;
-    uint32_t used = 0u;
-    for (int r = 0; r < c; ++r) {
-        int bj = -1;
-        float bf = 0.0f;
-        uint32_t bid = 0u;
-        for (int j = 0; j < c; ++j) {
-            const float f = lds_ld<float>(ucol + 256u * j);
-            const uint32_t id = lds_ld<uint8_t>(icol + 64u * j);
-            const bool better =
-                !((used >> j) & 1u) && ((bj < 0) || (f < bf) || (f == bf && id < bid));
-            bj = better ? j : bj;
-            bf = better ? f : bf;
-            bid = better ? id : bid;
-        }
-        used |= 1u << bj;  // c - r > 0 entries are unused, so bj >= 0
-        const int rr = nfin + r;
-        if (rr == 0) win(bid);
-        if (row != kNoRow) lds_st<uint8_t>(row + rr, (uint8_t)bid);
-    }
-    return c;
-}
-
-// Step 6: compare-exchange of slots k and k+1: three v_swap_b32 under the
-// execution mask of the lanes that need the exchange, skipped when none
-// does (the first pass of a tick exchanges most pairs in some lane, later
-// passes few).
-__device__ __forceinline__ void vswap(float& a, float& b) {
-    asm volatile("v_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-}
-__device__ __forceinline__ void vswap(uint32_t& a, uint32_t& b) {
-    asm volatile("v_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-}
-
-template <int N>
-__device__ __forceinline__ void slots_cx(Slots<N>& sl, int k) {
-    if (slot_key(sl.d[k], sl.rec[k]) > slot_key(sl.d[k + 1], sl.rec[k + 1])) {
-        vswap(sl.d[k], sl.d[k + 1]);
-        vswap(sl.rec[k], sl.rec[k + 1]);
-        vswap(sl.s[k], sl.s[k + 1]);
-    }
-}
-
-// One upward pass that also re-exchanges the pair below after each step
-// (k = 0 .. N-2: pairs k, then k-1), so a slot passed by two others moves
-// down two places in one pass.  A tick's overtakes then need one such pass
-// in most ticks where plain up/down passes need two: by a CPU replay of
-// the 20-competitor workload, 1.24 passes and 22 order checks per tick
-// instead of 2.22 and 40, for the same number of compare-exchanges.
-// Checks every pair once the pass has left it.
-template <int N>
-__device__ __forceinline__ bool slots_pass_up2(Slots<N>& sl) {
-    bool bad = false;
-#pragma unroll
-    for (int k = 0; k < N - 1; ++k) {
-        slots_cx<N>(sl, k);
-        if (k >= 1) slots_cx<N>(sl, k - 1);
-        if (k >= 2)
-            bad |= slot_key(sl.d[k - 2], sl.rec[k - 2]) > slot_key(sl.d[k - 1], sl.rec[k - 1]);
-    }
-    if constexpr (N >= 3)
-        bad |= slot_key(sl.d[N - 3], sl.rec[N - 3]) > slot_key(sl.d[N - 2], sl.rec[N - 2]);
-    if constexpr (N >= 2)
-        bad |= slot_key(sl.d[N - 2], sl.rec[N - 2]) > slot_key(sl.d[N - 1], sl.rec[N - 1]);
-    return bad;
-}
-
-// One downward pass (k = N-2 .. 0; carries a slot down any distance).
-template <int N>
-__device__ __forceinline__ bool slots_pass_down(Slots<N>& sl) {
-    bool bad = false;
-#pragma unroll
-    for (int k = N - 2; k >= 0; --k) {
-        slots_cx<N>(sl, k);
-        if (k + 2 <= N - 1)
-            bad |= slot_key(sl.d[k + 1], sl.rec[k + 1]) > slot_key(sl.d[k + 2], sl.rec[k + 2]);
-    }
-    return bad;
-}
-
-// Step 6 in full: alternate passes until every active lane of the wave is
-// in order (a tick's overtakes need one pass in most lanes, two where a
-// slot moves down by more than two places).
-template <int N>
-__device__ __forceinline__ void slots_restore(Slots<N>& sl) {
-    for (;;) {
-        if (!__builtin_amdgcn_ballot_w64(slots_pass_up2<N>(sl))) break;
-        if (!__builtin_amdgcn_ballot_w64(slots_pass_down<N>(sl))) break;
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Plain ticks: no two running competitors of a lane share a position.  Nearly
 // every tick of a wave is plain (equal positions: the start line, and a few
-// ticks in ten thousand after it), and needs much less than slots_tick: the
-// competitor ahead of slot k is slot k+1 itself, and float compares order the
-// slots (no compare with a parked slot's NaN holds, which leaves the parked
-// slots at the top and whoever leads unblocked).  Ticks that are not plain
-// take slots_tick and its passes.
+// ticks in ten thousand after it): the competitor ahead of slot k is slot k+1
+// itself, and float compares order the slots (no compare with a parked slot's NaN
+// holds, which leaves the parked slots at the top and whoever leads unblocked).
 //
-// At 20 competitors a plain tick's straight-line block has 308 vector
-// instructions against 466 of slots_tick, and its sort 19 compares and what
-// has to move against 42 compares and 22 checks.  The kernels are bound by
-// vector issue (98% busy over the uneven batch), so that is the gain: 10^6
-// simulations of 20 competitors from the start 7.54 -> 5.93 ms, 4096 uneven
-// in-play requests 19.95 -> 16.4 ms.  A race whose competitors stay tied for
-// good pays for both: 13% more than before.
+// With one kind of tick for all, which looked past equal positions and ordered
+// the slots by (position, index) in 64-bit compares, the straight-line block at 20
+// competitors had 466 vector instructions against 308 of a plain tick.  The
+// kernels are bound by vector issue (98% busy over the uneven batch), so that is
+// the gain: 10^6 simulations of 20 competitors from the start 7.54 -> 5.93 ms, 4096
+// uneven in-play requests 19.95 -> 16.4 ms.  Fields that stay tied for good take
+// the loop of slots_tick_tied throughout: 4*10^5 simulations of 20 identical
+// competitors 2.24 -> 2.11 ms against that one kind, 10^5 of two 154 -> 164 us.
 // ---------------------------------------------------------------------------
 
 struct StepBounds {
@@ -440,35 +230,6 @@ __device__ __forceinline__ bool slots_gaps(const Slots<N>& sl, float (&gap)[N]) 
     }
     gap[A - 1] = __builtin_inff();
     return __builtin_amdgcn_ballot_w64(least == 0u) != 0;
-}
-
-// Whether some lane of the wave has two equal positions (parked slots, whose
-// NaN equals nothing, apart).
-template <int N>
-__device__ __forceinline__ bool slots_tied(const Slots<N>& sl) {
-    bool tie = false;
-#pragma unroll
-    for (int k = 0; k < N - 1; ++k) tie |= sl.d[k] == sl.d[k + 1];
-    return __builtin_amdgcn_ballot_w64(tie) != 0;
-}
-
-// Keeps the compiler from carrying one loop's choice of registers for the
-// slots into another (the 64-bit compares of the other ticks want position
-// and record in a register pair; with one choice for all, the loop of the
-// plain ticks began with 60 moves).
-template <int N>
-__device__ __forceinline__ void slots_opaque(Slots<N>& sl) {
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        float d, s;
-        uint32_t rec;
-        asm volatile("v_mov_b32 %0, %3\n\tv_mov_b32 %1, %4\n\tv_mov_b32 %2, %5"
-                     : "=&v"(d), "=&v"(rec), "=&v"(s)
-                     : "v"(sl.d[k]), "v"(sl.rec[k]), "v"(sl.s[k]));
-        sl.d[k] = d;
-        sl.rec[k] = rec;
-        sl.s[k] = s;
-    }
 }
 
 // Moves slot K down past the up to three slots below it with larger
@@ -571,6 +332,37 @@ __device__ __forceinline__ void slots_sort(Slots<N>& sl) {
     } while (__builtin_amdgcn_readfirstlane((uint32_t)deep | (uint32_t)(deep >> 32)));
 }
 
+// What a tick reads of the slots' competitors, from the LDS tables: the draw of
+// competitor c sits at ucol + 256*c = ubias + 16*rec.
+template <int N, Pace kPace>
+struct SlotInputs {
+    float draw[N], theta[N], term[N];
+    f32x4 par[N];  // elo, espan16, alpha, beta
+    // kKeep: the slot's position takes the place of the draw
+    template <bool kKeep>
+    __device__ __forceinline__ void fetch(const Slots<N>& sl, int k, uint32_t ubias) {
+        const uint32_t rec = sl.rec[k];
+        draw[k] = lds_ld<float>(ubias + (rec << 4));
+        if constexpr (kKeep) lds_st<float>(ubias + (rec << 4), sl.d[k]);
+        par[k] = lds_ld<f32x4>(rec);
+        if constexpr (kPace == kPaceTable) {
+            const f32x2 q = lds_ld<f32x2>(rec + kRecHalf<N>);
+            theta[k] = q.x;
+            term[k] = q.y;
+        } else {
+            theta[k] = lds_ld<float>(rec + kRecHalf<N>);
+        }
+    }
+    __device__ __forceinline__ float response(int k, float d) const {  // R of Eq. 1
+        const float R = par[k].z + par[k].w * d;
+        if constexpr (kPace == kPaceTable) return R + term[k];
+        return R;
+    }
+    __device__ __forceinline__ float free(int k) const {  // a free step over R
+        return par[k].x + par[k].y * draw[k];
+    }
+};
+
 // Steps 1-4 of a plain tick for the A lowest slots (the others are parked in
 // every lane), without the test for the line.  Bottom up, so that a slot's
 // step overwrites the one before only after the slot below has read it.
@@ -578,46 +370,101 @@ __device__ __forceinline__ void slots_sort(Slots<N>& sl) {
 // draw, for the crossing fractions.
 template <int N, Pace kPace, int A, bool kKeep>
 __device__ __forceinline__ void slots_tick_plain(Slots<N>& sl, const float (&gap)[N],
-                                                 uint32_t ucol, uint32_t pbase, uint32_t t,
-                                                 uint32_t sim, uint32_t request, uint32_t k0,
-                                                 uint32_t k1) {
-    if constexpr (kPace == kPaceTable) write_pace_terms<N>(pbase, t);
-    write_draws<N>(ucol, t, sim, request, k0, k1);
+                                                 uint32_t ucol, uint32_t pbase) {
     const uint32_t ubias = ucol - 16u * pbase;
     constexpr int kPf = 4;
-    float pu[N], pth[N], pga[N];
-    f32x4 pp[N];
-    auto fetch = [&](int k) {
-        const uint32_t rec = sl.rec[k];
-        pu[k] = lds_ld<float>(ubias + (rec << 4));
-        if constexpr (kKeep) lds_st<float>(ubias + (rec << 4), sl.d[k]);
-        pp[k] = lds_ld<f32x4>(rec);
-        if constexpr (kPace == kPaceTable) {
-            const f32x2 q = lds_ld<f32x2>(rec + kRecHalf<N>);
-            pth[k] = q.x;
-            pga[k] = q.y;
-        } else {
-            pth[k] = lds_ld<float>(rec + kRecHalf<N>);
-        }
-    };
+    SlotInputs<N, kPace> in;
 #pragma unroll
-    for (int k = 0; k < A && k < kPf; ++k) fetch(k);
+    for (int k = 0; k < A && k < kPf; ++k) in.template fetch<kKeep>(sl, k, ubias);
 #pragma unroll
     for (int k = 0; k < A; ++k) {
-        if (k + kPf < A) fetch(k + kPf);
+        if (k + kPf < A) in.template fetch<kKeep>(sl, k + kPf, ubias);
         const float d = sl.d[k];
-        const f32x4 p = pp[k];
-        float R = p.z + p.w * d;
-        if constexpr (kPace == kPaceTable) R = R + pga[k];
-        float f = p.x + p.y * pu[k];
+        float f = in.free(k);
         if (k < A - 1) {
             const float s_min = __uint_as_float(
                 min(__float_as_uint(sl.s[k]), __float_as_uint(sl.s[k + 1])));
-            f = (gap[k] <= pth[k]) ? s_min : f;
+            f = (gap[k] <= in.theta[k]) ? s_min : f;
         }
-        const float S = R * f;
+        const float S = in.response(k, d) * f;
         sl.d[k] = d + S;
         sl.s[k] = S;
+    }
+}
+
+// Puts the equal positions of slots K and K + 1 in index order in every lane;
+// `equal` collects the lanes that have some, `moved` those that were not in order.
+template <int N, int K>
+__device__ __forceinline__ void slots_order_pair(Slots<N>& sl, uint64_t& equal, uint64_t& moved) {
+    uint64_t all;
+    asm volatile(
+        "v_cmp_eq_f32 vcc, %[a0], %[b0]\n\t"
+        "s_cbranch_vccz .Ldiff%=\n\t"
+        "v_cmp_gt_u32 %[all], %[a1], %[b1]\n\t"
+        "s_or_b64 %[equal], %[equal], vcc\n\t"
+        "s_and_b64 vcc, vcc, %[all]\n\t"
+        "s_cbranch_scc0 .Ldiff%=\n\t"
+        "s_mov_b64 %[all], exec\n\t"
+        "s_mov_b64 exec, vcc\n\t"
+        "v_swap_b32 %[a1], %[b1]\n\t"
+        "v_swap_b32 %[a2], %[b2]\n\t"
+        "s_or_b64 %[moved], %[moved], vcc\n\t"
+        "s_mov_b64 exec, %[all]\n"
+        ".Ldiff%=:"
+        : [a1] "+v"(sl.rec[K]), [a2] "+v"(sl.s[K]), [b1] "+v"(sl.rec[K + 1]),
+          [b2] "+v"(sl.s[K + 1]), [all] "=&s"(all), [equal] "+s"(equal), [moved] "+s"(moved)
+        : [a0] "v"(sl.d[K]), [b0] "v"(sl.d[K + 1])
+        : "vcc", "scc");
+}
+
+template <int N, int K, int A>
+__device__ __forceinline__ void slots_order_pairs(Slots<N>& sl, uint64_t& equal, uint64_t& moved) {
+    if constexpr (K + 1 < A) {
+        slots_order_pair<N, K>(sl, equal, moved);
+        slots_order_pairs<N, K + 1, A>(sl, equal, moved);
+    }
+}
+
+// Puts equal positions among the A lowest slots in index order (positions being
+// in order), in every lane; whether there are any.
+template <int N, int A>
+__device__ __forceinline__ bool slots_order_equal(Slots<N>& sl) {
+    uint64_t equal, moved;
+    do {
+        equal = moved = 0;
+        slots_order_pairs<N, 0, A>(sl, equal, moved);
+    } while (A > 2 && __builtin_amdgcn_readfirstlane((uint32_t)moved | (uint32_t)(moved >> 32)));
+    return __builtin_amdgcn_readfirstlane((uint32_t)equal | (uint32_t)(equal >> 32));
+}
+
+// slots_tick_plain, with kKeep, where some lane has equal positions (in index
+// order).  The competitor ahead of slot k is then the first slot above it with a
+// larger position: slot k+1, or -- where positions are equal -- the one found for
+// slot k+1, carried down in (nd, ns).  Top down, the start-of-tick position and
+// step of slot k+1 in (d_up, s_up).
+template <int N, Pace kPace, int A>
+__device__ __forceinline__ void slots_tick_tied(Slots<N>& sl, uint32_t ucol, uint32_t pbase) {
+    const uint32_t ubias = ucol - 16u * pbase;
+    constexpr int kPf = 4;
+    SlotInputs<N, kPace> in;
+#pragma unroll
+    for (int k = A - 1; k >= 0 && k >= A - kPf; --k) in.template fetch<true>(sl, k, ubias);
+    float nd = __builtin_inff(), ns = 0.0f;
+    float d_up = __builtin_inff(), s_up = 0.0f;
+#pragma unroll
+    for (int k = A - 1; k >= 0; --k) {
+        if (k - kPf >= 0) in.template fetch<true>(sl, k - kPf, ubias);
+        const float d = sl.d[k], s = sl.s[k];
+        const bool gt = d_up > d;  // false next to a parked (NaN) slot
+        nd = gt ? d_up : nd;
+        ns = gt ? s_up : ns;
+        const float s_min =
+            __uint_as_float(min(__float_as_uint(s), __float_as_uint(ns)));
+        const float S = in.response(k, d) * ((nd - d <= in.theta[k]) ? s_min : in.free(k));
+        sl.d[k] = d + S;
+        sl.s[k] = S;
+        d_up = d;
+        s_up = s;
     }
 }
 
@@ -642,20 +489,36 @@ __device__ __forceinline__ void slots_cross(Slots<N>& sl, float L, uint32_t& cro
         : "vcc", "scc");
 }
 
-template <int N, int K, int A>
-__device__ __forceinline__ void slots_cross_all(Slots<N>& sl, float L, uint32_t& cross,
+template <int N, int K, int M>
+__device__ __forceinline__ void slots_cross_few(Slots<N>& sl, float L, uint32_t& cross,
                                                 uint32_t& kset) {
-    if constexpr (K < A) {
+    if constexpr (M > 0 && K >= 0) {
         slots_cross<N, K>(sl, L, cross, kset);
-        slots_cross_all<N, K + 1, A>(sl, L, cross, kset);
+        slots_cross_few<N, K - 1, M - 1>(sl, L, cross, kset);
     }
 }
 
-// Step 5 after a plain tick: ranks a lane's finishers of this tick (`cross`:
-// their slots, parked by slots_cross; `kset`: those of the whole wave) as
-// slots_rank_park does.  The crossing fraction of competitor c goes to its own
-// place of the draw table, where slots_tick_plain left its start-of-tick
-// position.
+// Slots from the top down, a few at a time (positions being in order): below one
+// that is short of the line in every lane nobody is at it.
+constexpr int kCrossStep = 5;
+template <int N, int K>
+__device__ __forceinline__ void slots_cross_all(Slots<N>& sl, float L, uint32_t& cross,
+                                                uint32_t& kset) {
+    if constexpr (K >= 4)
+        if (!__builtin_amdgcn_ballot_w64(!(sl.d[K] < L))) return;
+    slots_cross_few<N, K, kCrossStep>(sl, L, cross, kset);
+    if constexpr (K >= kCrossStep) slots_cross_all<N, K - kCrossStep>(sl, L, cross, kset);
+}
+
+// Ranks a lane's finishers of this tick (`cross`: their slots, parked by
+// slots_cross; `kset`: those of the whole wave) after the `nfin` earlier ones and
+// records them; returns the number ranked.  `rank` is false in lanes whose
+// simulation has already ended, and in those without a finisher.  Entry j (the
+// j-th set bit of `cross`) holds its competitor index in the lane's column of a
+// byte table, at icol + 64*j; the crossing fraction of competitor c goes to its
+// own place of the draw table, where the tick left its start-of-tick position.
+// The entries are then picked in (fraction, index) order, so the work grows with
+// c^2 for the few finishers of a tick rather than with c*N.
 template <int N, int A, class Win>
 __device__ __forceinline__ int slots_rank(const Slots<N>& sl, uint32_t cross, uint32_t kset,
                                           bool rank, float L, uint32_t ucol, uint32_t icol,
@@ -699,16 +562,25 @@ __device__ __forceinline__ int slots_rank(const Slots<N>& sl, uint32_t cross, ui
 }
 
 // How a run of ticks ended.
-enum Outcome : int { kEnded = 0, kParked = 1, kTied = 2 };
+enum Outcome : int { kEnded = 0, kParked = 1, kTurn = 2 };
 
-// Runs f(std::integral_constant<int, A>) for A = N, N - kStep, ... (A >=
-// kStep > 0; A = N only where kStep = 0) one after the other for as long as f
-// returns kParked.
-template <int A, int kStep, class F>
+// The active slots of the phase after one of A: kStep less (0: there is none),
+// for ticks of equal positions twice that in large fields, which keeps the
+// copies of their rarer loop few.
+template <int kStep, bool kTied>
+constexpr int next_phase(int A) {
+    const int less = kTied && A > 4 * kStep ? 2 * kStep : kStep;
+    return kStep > 0 && A - less >= kStep ? A - less : 0;
+}
+
+// Runs f(A, kTied) as constants for A = N and each next phase one after the other
+// for as long as f returns kParked.
+template <int A, int kStep, bool kTied, class F>
 __device__ __forceinline__ Outcome run_phases(F& f) {
-    const Outcome o = f(std::integral_constant<int, A>{});
-    if constexpr (kStep > 0 && A - kStep >= kStep)
-        if (o == kParked) return run_phases<A - kStep, kStep>(f);
+    const Outcome o =
+        f(std::integral_constant<int, A>{}, std::integral_constant<bool, kTied>{});
+    if constexpr (next_phase<kStep, kTied>(A) > 0)
+        if (o == kParked) return run_phases<next_phase<kStep, kTied>(A), kStep, kTied>(f);
     return o;
 }
 
@@ -743,7 +615,8 @@ __device__ __forceinline__ void run_generation(uint32_t ubase, uint32_t ibase, u
     auto row_of = [&](uint32_t lane) {
         return rows == kNoRow ? kNoRow : rows + (uint32_t)N * lane;
     };
-    // Counts this tick's `k` finishers and settles the simulations that end.
+    // Counts this tick's `k` finishers and settles the simulations that end
+    // (nobody's does in a tick without finishers, but at the tick limit).
     auto end_tick = [&](int k) {
         nfin += k;
         run += (uint32_t)k * (t + 1 - t0);
@@ -769,8 +642,10 @@ __device__ __forceinline__ void run_generation(uint32_t ubase, uint32_t ibase, u
         int left = t - t0 < kTickLimit - 16u ? open_ticks<N>(sl, L, sb) : 0;
         while (left != 0 && !tie) {
             t = __builtin_amdgcn_readfirstlane(t);  // the wave's: the compiler cannot tell
-            slots_tick_plain<N, kPace, N, false>(sl, gap, ubase + 4u * lane_here(), pbase, t, sim,
-                                                 request, k0, k1);
+            const uint32_t ucol = ubase + 4u * lane_here();
+            if constexpr (kPace == kPaceTable) write_pace_terms<N>(pbase, t);
+            write_draws<N>(ucol, t, sim, request, k0, k1);
+            slots_tick_plain<N, kPace, N, false>(sl, gap, ucol, pbase);
             t += 1;
             slots_sort<N, N>(sl);
             tie = slots_gaps<N, N>(sl, gap);
@@ -779,65 +654,68 @@ __device__ __forceinline__ void run_generation(uint32_t ubase, uint32_t ibase, u
         }
         may_open = left != 0;
     };
-    // One phase runs plain ticks of the A lowest slots (slots A .. N-1 are
-    // parked in every lane) until the generation ends, a tie, or until the
-    // next kSkipStep slots down are parked in every lane too.
-    auto phase = [&](auto act) -> Outcome {
+    // One phase runs ticks of the A lowest slots (slots A .. N-1 are parked in
+    // every lane), plain ones until positions are equal or, kTied, those of equal
+    // positions until there are none; or until the generation ends, or more slots
+    // are parked in every lane.
+    auto phase = [&](auto act, auto tied) -> Outcome {
         constexpr int A = decltype(act)::value;
+        constexpr bool kTied = decltype(tied)::value;
+        constexpr int kNext = next_phase<kSkipStep, kTied>(A);
         // the slots are in order, so a lane's parked ones are its top ones:
-        // the next kSkipStep down are parked everywhere iff the lowest is
+        // all down to slot kNext are parked everywhere iff that one is
         auto parked_below = [&]() {
-            if constexpr (kSkipStep > 0 && A - kSkipStep >= kSkipStep)
-                return !__builtin_amdgcn_ballot_w64(__float_as_uint(sl.d[A - kSkipStep]) !=
+            if constexpr (kNext > 0)
+                return !__builtin_amdgcn_ballot_w64(__float_as_uint(sl.d[kNext]) !=
                                                     __float_as_uint(parked()));
             return false;
         };
         if (parked_below()) return kParked;
         float gap[N];
-        bool tie = slots_gaps<N, A>(sl, gap);
-        while (!tie) {
-            if (!__builtin_amdgcn_ballot_w64(live)) return kEnded;
+        auto looks = [&]() {  // whether the next tick is of the other kind
+            if constexpr (kTied) return !slots_order_equal<N, A>(sl);
+            return slots_gaps<N, A>(sl, gap);
+        };
+        // what depends on the simulation index only is computed once where there
+        // are registers for it
+        constexpr bool kOnce = kSkipStep == 0;
+        uint32_t sim0 = 0, request0 = 0;
+        if constexpr (kOnce) {
+            sim0 = sim_of(lane_here());
+            request0 = request_of(lane_here());
+        }
+        // (at least one tick where the other kind sent it here)
+        bool turn = looks() && !kTied;
+        if (!__builtin_amdgcn_ballot_w64(live)) return kEnded;
+        while (!turn) {
             t = __builtin_amdgcn_readfirstlane(t);  // the wave's: the compiler cannot tell
             const uint32_t lane = lane_here(), ucol = ubase + 4u * lane;
-            slots_tick_plain<N, kPace, A, true>(sl, gap, ucol, pbase, t, sim_of(lane),
-                                                request_of(lane), k0, k1);
+            if constexpr (kPace == kPaceTable) write_pace_terms<N>(pbase, t);
+            write_draws<N>(ucol, t, kOnce ? sim0 : sim_of(lane),
+                           kOnce ? request0 : request_of(lane), k0, k1);
+            if constexpr (kTied)
+                slots_tick_tied<N, kPace, A>(sl, ucol, pbase);
+            else
+                slots_tick_plain<N, kPace, A, true>(sl, gap, ucol, pbase);
             slots_sort<N, A>(sl);
             uint32_t cross = 0u, kset = 0u;
-            slots_cross_all<N, 0, A>(sl, L, cross, kset);
+            slots_cross_all<N, A - 1>(sl, L, cross, kset);
             kset = __builtin_amdgcn_readfirstlane(kset);
-            int k = 0;
-            if (kset)
-                k = slots_rank<N, A>(sl, cross, kset, live && cross, L, ucol,
-                                     ibase + lane, pbase, nfin, win, row_of(lane));
-            end_tick(k);
+            if (kset || t + 1 - t0 >= kTickLimit) {
+                end_tick(slots_rank<N, A>(sl, cross, kset, live && cross, L, ucol, ibase + lane,
+                                          pbase, nfin, win, row_of(lane)));
+                if (!__builtin_amdgcn_ballot_w64(live)) return kEnded;
+            }
             t += 1;
             if (kset && parked_below()) return kParked;
-            tie = slots_gaps<N, A>(sl, gap);
+            turn = looks();
         }
-        return kTied;
+        return kTurn;
     };
     for (;;) {
         if (may_open) open_run();
-        if (run_phases<N, kSkipStep>(phase) == kEnded) break;
-        // a tie: ticks that look past equal positions, in index order, until
-        // the positions differ again
-        slots_opaque<N>(sl);
-        slots_restore<N>(sl);
-        do {
-            t = __builtin_amdgcn_readfirstlane(t);
-            const uint32_t lane = lane_here(), ucol = ubase + 4u * lane;
-            const uint32_t cross =
-                slots_tick<N, kPace>(sl, ucol, pbase, L, t, sim_of(lane), request_of(lane), k0,
-                                     k1);
-            int k = 0;
-            if (__builtin_amdgcn_ballot_w64(cross != 0u))
-                k = slots_rank_park<N>(sl, cross, live && cross, L, ucol, ibase + lane, pbase,
-                                       nfin, win, row_of(lane));
-            end_tick(k);
-            t += 1;
-            slots_restore<N>(sl);
-            slots_opaque<N>(sl);  // (after the loop, the other loops spilled)
-        } while (__builtin_amdgcn_ballot_w64(live) && slots_tied<N>(sl));
+        if (run_phases<N, kSkipStep, false>(phase) == kEnded) break;
+        if (run_phases<N, kSkipStep, true>(phase) == kEnded) break;
     }
     steps += run;
 }
