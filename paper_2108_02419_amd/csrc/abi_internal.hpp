@@ -9,6 +9,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <exception>
 #include <string>
 
 #define BBE_API extern "C" __attribute__((visibility("default")))
@@ -38,6 +39,17 @@ inline int fail(int code, const char* fmt, ...) {
 inline int ok() {
     g_err.clear();
     return BBE_OK;
+}
+
+// Runs the body of an entry point that allocates host memory by its input's
+// size: what the standard library throws where there is none ends here.
+template <class F>
+int guarded(const F& body) {
+    try {
+        return body();
+    } catch (const std::exception&) {
+        return fail(BBE_ENOMEM, "out of host memory");
+    }
 }
 
 // Host-side fault injection, for the tests of the error paths.  The

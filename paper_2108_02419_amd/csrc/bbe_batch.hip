@@ -585,15 +585,12 @@ bool same_state(const bbe_state* a, const bbe_state* b, int n) {
 
 }  // namespace
 
-BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t seed,
-                                  uint64_t* win_counts, double* probs, uint64_t* step_count,
-                                  unsigned flags, void* stream, bbe_batch_plan** out) {
-    if (!out) return fail(BBE_EINVAL, "out is NULL");
-    *out = nullptr;
-    if (!reqs || n_reqs < 1) return fail(BBE_EINVAL, "need n_reqs >= 1 requests");
-    if (!win_counts) return fail(BBE_EINVAL, "win_counts is NULL");
-    bbe_batch_plan* p = new (std::nothrow) bbe_batch_plan();
-    if (!p) return fail(BBE_ENOMEM, "out of host memory");
+namespace {
+
+// Makes plan p for the requests; the caller destroys it where this fails.
+int make_plan(bbe_batch_plan* p, const bbe_request* reqs, int n_reqs, uint64_t seed,
+              uint64_t* win_counts, double* probs, uint64_t* step_count, unsigned flags,
+              void* stream) {
     p->n_reqs = n_reqs;
     p->table.resize((size_t)n_reqs * (sizeof(bbe::ReqDesc) + sizeof(bbe::StartState)) +
                     states_at(n_reqs));
@@ -623,20 +620,16 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
             } else if (q.race) rc = fail(rc, "request %d: %s", i, g_err.c_str());
         }
         if (rc != BBE_OK) {
-            destroy(p);
-            return rc;
+                return rc;
         }
         if (q.n_sims == 0) {
-            destroy(p);
-            return fail(BBE_EINVAL, "request %d: n_sims must be >= 1", i);
+                return fail(BBE_EINVAL, "request %d: n_sims must be >= 1", i);
         }
         if ((uint64_t)q.sim_begin + q.n_sims > 0x100000000ull) {
-            destroy(p);
-            return fail(BBE_EINVAL, "request %d: sim_begin + n_sims exceeds 2^32", i);
+                return fail(BBE_EINVAL, "request %d: sim_begin + n_sims exceeds 2^32", i);
         }
         if (q.stop_after < 0 || q.stop_after > q.race->n) {
-            destroy(p);
-            return fail(BBE_EINVAL, "request %d: stop_after = %d outside 0..%d", i,
+                return fail(BBE_EINVAL, "request %d: stop_after = %d outside 0..%d", i,
                         q.stop_after, q.race->n);
         }
         bbe::ReqDesc& d = descs[i];
@@ -665,17 +658,14 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
     hipError_t e;
     if (dev_alloc(&p->d_reqs, p->table.size()) != hipSuccess ||
         dev_alloc(&p->d_queue, sizeof(uint32_t) * bbe::kMaxN) != hipSuccess) {
-        destroy(p);
         return fail(BBE_ENOMEM, "device allocation of the request table failed");
     }
     if ((e = BBE_HIP(hipMemcpy(p->d_reqs, p->table.data(), p->used, hipMemcpyHostToDevice))) !=
         hipSuccess) {
-        destroy(p);
         return hip_fail(e, "copying the request table");
     }
     if ((e = BBE_HIP(hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking))) !=
         hipSuccess) {
-        destroy(p);
         return hip_fail(e, "creating the capture stream");
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -725,8 +715,7 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
             if (rc != BBE_OK) {
                 (void)hipEventDestroy(ev0);
                 (void)hipEventDestroy(ev1);
-                destroy(p);
-                return rc;
+                        return rc;
             }
             float ms_min = 1e30f;
             bool okc = true;
@@ -753,29 +742,17 @@ BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t 
     int rc = upload_work(p, best, requests(p), state_of, states);
     if (rc == BBE_OK) rc = capture(p);
     if (rc != BBE_OK) {
-        destroy(p);
         return rc;
     }
 
     if ((e = hipStreamSynchronize(s)) != hipSuccess) {
-        destroy(p);
         return hip_fail(e, "synchronizing after plan set-up");
     }
-    *out = p;
-    return ok();
+    return BBE_OK;
 }
 
-BBE_API int bbe_batch_plan_launch(bbe_batch_plan* plan, void* stream) {
-    if (!plan || !plan->exec) return fail(BBE_EINVAL, "plan is NULL");
-    hipError_t e = BBE_HIP(hipGraphLaunch(plan->exec, static_cast<hipStream_t>(stream)));
-    if (e != hipSuccess) return hip_fail(e, "launching the plan graph");
-    return ok();
-}
-
-BBE_API int bbe_batch_plan_set_states(bbe_batch_plan* plan, const bbe_state* states,
-                                      void* stream) {
-    if (!plan || !plan->exec) return fail(BBE_EINVAL, "plan is NULL");
-    if (!states) return fail(BBE_EINVAL, "states is NULL");
+// Gives the plan's requests new states.
+int point_plan(bbe_batch_plan* plan, const bbe_state* states, void* stream) {
     const int n_reqs = plan->n_reqs;
     // validate every state before touching the plan; a request in the state of
     // the one before it in its group shares that one's entry
@@ -809,6 +786,42 @@ BBE_API int bbe_batch_plan_set_states(bbe_batch_plan* plan, const bbe_state* sta
                                           to - from, hipMemcpyHostToDevice, s));
     if (e != hipSuccess) return hip_fail(e, "copying the request table");
     return ok();
+}
+
+}  // namespace
+
+BBE_API int bbe_batch_plan_create(const bbe_request* reqs, int n_reqs, uint64_t seed,
+                                  uint64_t* win_counts, double* probs, uint64_t* step_count,
+                                  unsigned flags, void* stream, bbe_batch_plan** out) {
+    if (!out) return fail(BBE_EINVAL, "out is NULL");
+    *out = nullptr;
+    if (!reqs || n_reqs < 1) return fail(BBE_EINVAL, "need n_reqs >= 1 requests");
+    if (!win_counts) return fail(BBE_EINVAL, "win_counts is NULL");
+    bbe_batch_plan* p = new (std::nothrow) bbe_batch_plan();
+    if (!p) return fail(BBE_ENOMEM, "out of host memory");
+    const int rc = guarded([&] {
+        return make_plan(p, reqs, n_reqs, seed, win_counts, probs, step_count, flags, stream);
+    });
+    if (rc != BBE_OK) {
+        destroy(p);
+        return rc;
+    }
+    *out = p;
+    return ok();
+}
+
+BBE_API int bbe_batch_plan_launch(bbe_batch_plan* plan, void* stream) {
+    if (!plan || !plan->exec) return fail(BBE_EINVAL, "plan is NULL");
+    hipError_t e = BBE_HIP(hipGraphLaunch(plan->exec, static_cast<hipStream_t>(stream)));
+    if (e != hipSuccess) return hip_fail(e, "launching the plan graph");
+    return ok();
+}
+
+BBE_API int bbe_batch_plan_set_states(bbe_batch_plan* plan, const bbe_state* states,
+                                      void* stream) {
+    if (!plan || !plan->exec) return fail(BBE_EINVAL, "plan is NULL");
+    if (!states) return fail(BBE_EINVAL, "states is NULL");
+    return guarded([&] { return point_plan(plan, states, stream); });
 }
 
 BBE_API int bbe_batch_plan_info(const bbe_batch_plan* plan, int* waves_per_block, int* grid,

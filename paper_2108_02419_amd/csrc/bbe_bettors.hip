@@ -51,32 +51,9 @@ BBE_API int bbe_race_trace(const bbe_race* race, const bbe_state* state, uint64_
     return ok();
 }
 
-BBE_API int bbe_bettors_create(const uint8_t* kind, const float* param, int n_bettors,
-                               bbe_bettors** out) {
-    if (!out) return fail(BBE_EINVAL, "out is NULL");
-    *out = nullptr;
-    if (!kind || !param) return fail(BBE_EINVAL, "NULL argument");
-    if (n_bettors < 1) return fail(BBE_EINVAL, "n_bettors must be >= 1");
-    for (int b = 0; b < n_bettors; ++b) {
-        const float p = param[b];
-        switch (kind[b]) {
-            case BBE_BETTOR_ZI:
-            case BBE_BETTOR_LW:
-                break;
-            case BBE_BETTOR_UD:
-                if (!std::isfinite(p) || !(p >= 0.0f))
-                    return fail(BBE_EINVAL, "bettor %d: UD distance must be finite and >= 0", b);
-                break;
-            case BBE_BETTOR_LINEX:
-                if (!(p >= 1.0f && p <= (float)BBE_TICK_LIMIT) || p != std::floor(p))
-                    return fail(BBE_EINVAL,
-                                "bettor %d: LinEx window must be an integer in 1..BBE_TICK_LIMIT",
-                                b);
-                break;
-            default:
-                return fail(BBE_EINVAL, "bettor %d: unknown kind %d", b, (int)kind[b]);
-        }
-    }
+// Puts a checked population on the device.
+static int make_bettors(const uint8_t* kind, const float* param, int n_bettors,
+                        bbe_bettors** out) {
     // slices of consecutive bettors, each grouped by kind, keeping the
     // caller's order within a kind
     std::vector<uint32_t> order((size_t)n_bettors);
@@ -117,6 +94,35 @@ BBE_API int bbe_bettors_create(const uint8_t* kind, const float* param, int n_be
     }
     *out = b;
     return ok();
+}
+
+BBE_API int bbe_bettors_create(const uint8_t* kind, const float* param, int n_bettors,
+                               bbe_bettors** out) {
+    if (!out) return fail(BBE_EINVAL, "out is NULL");
+    *out = nullptr;
+    if (!kind || !param) return fail(BBE_EINVAL, "NULL argument");
+    if (n_bettors < 1) return fail(BBE_EINVAL, "n_bettors must be >= 1");
+    for (int b = 0; b < n_bettors; ++b) {
+        const float p = param[b];
+        switch (kind[b]) {
+            case BBE_BETTOR_ZI:
+            case BBE_BETTOR_LW:
+                break;
+            case BBE_BETTOR_UD:
+                if (!std::isfinite(p) || !(p >= 0.0f))
+                    return fail(BBE_EINVAL, "bettor %d: UD distance must be finite and >= 0", b);
+                break;
+            case BBE_BETTOR_LINEX:
+                if (!(p >= 1.0f && p <= (float)BBE_TICK_LIMIT) || p != std::floor(p))
+                    return fail(BBE_EINVAL,
+                                "bettor %d: LinEx window must be an integer in 1..BBE_TICK_LIMIT",
+                                b);
+                break;
+            default:
+                return fail(BBE_EINVAL, "bettor %d: unknown kind %d", b, (int)kind[b]);
+        }
+    }
+    return guarded([&] { return make_bettors(kind, param, n_bettors, out); });
 }
 
 BBE_API void bbe_bettors_free(bbe_bettors* b) { destroy(b); }
