@@ -241,14 +241,15 @@ typedef struct bbe_request {
 
 typedef struct bbe_batch_plan bbe_batch_plan;
 
-/* Plan flag: where several launch shapes (waves per workgroup, simulations
- * per work item, workgroups per CU) may be the best for the batch's size, time
- * them on the batch itself and keep the fastest; the choice is cached per device and batch size class for later
- * plans, in memory and in a JSON file ($BBE_TUNE_CACHE if set, an empty
- * value for none; else $XDG_CACHE_HOME/bbe/tune.json or
- * $HOME/.cache/bbe/tune.json) keyed by the device (architecture, name, CU
- * count) and the library's kernel sources, so that later processes skip
- * the timing. */
+/* Plan flag: from 16384 generations of 64 simulations on, time work items of one
+ * and of two generations on the batch itself and keep the faster; below, one
+ * generation is the best without timing.  The choice is cached per device and
+ * batch size class for later plans, in memory and in a JSON file
+ * ($BBE_TUNE_CACHE if set, an empty value for none; else
+ * $XDG_CACHE_HOME/bbe/tune.json or $HOME/.cache/bbe/tune.json) keyed by the
+ * device (architecture, name, CU count) and the library's kernel sources, so that
+ * later processes skip the timing.  A shape that the file holds is used as it is
+ * (simulations per work item, waves per workgroup, share of the CUs). */
 #define BBE_PLAN_AUTOTUNE 1u
 
 /* Builds a plan for n_reqs (>= 1) requests (the many dry-run requests of

@@ -18,6 +18,8 @@ using namespace bbe_abi;
 
 namespace {
 
+// Launch shape.  The tuner chooses among sims_per_item alone; the others are kept
+// for shapes that a tuning file holds.
 struct Shape {
     int waves_per_block;
     int sims_per_item;  // multiple of 64: one work item = sims_per_item / 64 generations

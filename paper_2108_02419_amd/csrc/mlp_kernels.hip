@@ -321,8 +321,9 @@ __global__ void __launch_bounds__(kMlpThreads) mlp_kernel(const MlpArgs a) {
     const int n = nb0 * 16 + (lane & 15);
     // With few workgroups there is nothing else on the CU to hide a fetch, so
     // fragments are fetched two layers ahead (two of the three sets of
-    // registers are then in flight); otherwise one layer ahead, in registers
-    // that leave room for a second workgroup.
+    // registers are then in flight); otherwise one layer ahead: at 32 rows the
+    // registers and 52 KB of LDS leave room for a second workgroup; at 64 rows
+    // LDS (104 KB) holds one a CU, and the registers go to the accumulators.
     constexpr bool kDeep = kTrain || RB == 1;
     floatx4 acc[RB][2];
     RowInputs<RB, kTrain> ri;

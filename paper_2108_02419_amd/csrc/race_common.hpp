@@ -68,10 +68,13 @@ __device__ __forceinline__ U4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c
     for (int r = 0; r < 10; ++r) {
         uint64_t p0 = (uint64_t)c0 * 0xD2511F53u;
         uint64_t p1 = (uint64_t)c2 * 0xCD9E8D57u;
-        // In the race kernels the counter words t, request and block are
+        // In race_mc_kernel the counter words t, request and block are
         // wave-uniform and only `sim` varies per lane, so the first rounds
         // mix at most one lane-varying word into each xor: plain xors let
-        // the compiler keep the uniform parts on the scalar unit there.
+        // the compiler keep the uniform parts on the scalar unit there.  (In
+        // batches `request` varies by lane too, t and block are uniform; in
+        // the team kernels all but the key may vary, and three plain xors
+        // more are what that costs.)
         uint32_t n0, n2;
         if (r < 3) {
             n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;

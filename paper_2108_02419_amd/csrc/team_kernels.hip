@@ -381,12 +381,17 @@ hipError_t launch_race_prefix(const PrefixArgs& a, hipStream_t s) {
 // fraction of that, but of every wave they fill, so the line lies where their
 // waves begin to queue: at so many simulations per competitor for teams of 8,
 // 16 and 32 lanes.  Measured on both sides, full orders, us (team / lane):
-//   n = 5   1000: 111 / 235    30720: 167 / 236     40960: 188 / 236
-//   n = 8  49152: 222 / 338    65536: 277 / 338
-//   n = 13  8192: 176 / 600    31200: 452 / 605     41600: 559 / 605
-//   n = 17 19125: 607 / 935    25500: 736 / 935
-//   n = 20  8192: 305 / 940    22500: 686 / 940     30000: 861 / 940
-// One competitor needs no look at the others: a lane each, 80 against 105.
+//   n = 2   1000: 116 / 139     8192: 118 / 139     16384: 123 / 139
+//   n = 3   1000: 120 / 181    12288: 125 / 181     24576: 139 / 181
+//   n = 4   1000: 120 / 220    16384: 128 / 220     32768: 155 / 220
+//   n = 5   1000: 128 / 261    30720: 176 / 261     40960: 200 / 261
+//   n = 8  49152: 237 / 362    65536: 298 / 362
+//   n = 13 10400: 219 / 601    31200: 443 / 601     41600: 577 / 601
+//   n = 17 19125: 607 / 805    25500: 760 / 805
+//   n = 20  7500: 299 / 948    22500: 676 / 948     30000: 884 / 948
+// The lead is least where a run is short (to the winner with a tenth of the track
+// to go, n = 8, 65536: 69 / 65).  One competitor needs no look at the others: a
+// lane each, 80 against 105.
 bool team_mc_fits(int n, uint32_t n_sims) {
     if (n < 2) return false;
     const uint32_t per = n <= 8 ? 8192u : n <= 16 ? 3200u : 1500u;
