@@ -188,12 +188,12 @@ __device__ __forceinline__ void write_draws(uint32_t ucol, uint32_t t, uint32_t 
 //
 // With one kind of tick for all, which looked past equal positions and ordered
 // the slots by (position, index) in 64-bit compares, the straight-line block at 20
-// competitors had 466 vector instructions against 308 of a plain tick.  The
+// competitors had 466 vector instructions against 313 of an open tick.  The
 // kernels are bound by vector issue (98% busy over the uneven batch), so that is
 // the gain: 10^6 simulations of 20 competitors from the start 7.54 -> 5.93 ms, 4096
 // uneven in-play requests 19.95 -> 16.4 ms.  Fields that stay tied for good take
 // the loop of slots_tick_tied throughout: 4*10^5 simulations of 20 identical
-// competitors 2.24 -> 2.11 ms against that one kind, 10^5 of two 154 -> 164 us.
+// competitors 2.24 -> 2.11 ms against that one kind, 10^5 of two 154 -> 161 us.
 // ---------------------------------------------------------------------------
 
 struct StepBounds {
